@@ -367,10 +367,12 @@ constexpr int gemm_lds_floats()
 // Accumulator register r of a 32x32 block holds row 8*(r/4) + 4*h + r%4, column lane%32.  What a block reads (C for
 // beta != 0, the tanh outputs) is loaded for all its 16 registers before the first store: C may alias what is read, so
 // the compiler keeps loads and stores of single elements in order and every one of the 128 of a 64 x 128 sub-tile
-// would wait for its own load.
-template <int TM, int TN, int EPI>
+// would wait for its own load.  SCALED: what leaves is the accumulator times `even` or `odd`, by its row (the addition of
+// +0 keeps a zero sum positive under a negative factor).
+template <int TM, int TN, int EPI, bool SCALED = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, const floatx16 (&acc)[TM][TN], const int row0,
-                                              const int col0, const int l32, const int h, float *Cout, const int ldc)
+                                              const int col0, const int l32, const int h, float *Cout, const int ldc,
+                                              const float even = 1.f, const float odd = 1.f)
 {
     if (row0 >= g.M || col0 >= g.N) return;
     // addresses: a part that is uniform over the wavefront (row0, col0 are) plus one lane offset
@@ -399,7 +401,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, const floatx16 
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float v = acc[x][y][r];
+                const float v = SCALED ? __builtin_fmaf(acc[x][y][r], (r & 1) ? odd : even, 0.f) : acc[x][y][r];
                 float out;
                 if (EPI == EPI_AXPBY) {
                     out = g.alpha * v;
