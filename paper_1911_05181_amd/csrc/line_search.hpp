@@ -92,11 +92,12 @@ __global__ __launch_bounds__(256) void ls_slope_row_kernel(const float *__restri
         s *= scale;
         t *= scale;
         m = nm;
+        const float base_m = m == -INFINITY ? 0.f : m;         // (only logits of -inf so far: they weigh nothing, not NaN)
 #pragma unroll
         for (int v = 0; v < V; ++v) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float x = __expf(a[v][e] - m);
+                const float x = __expf(a[v][e] - base_m);
                 s += x;
                 t += x * d[v][e];
             }
