@@ -167,21 +167,22 @@ constexpr unsigned ALL_CFGS = (1u << CFG_COUNT) - 1;
 // ---------------------------------------------------------------------------------------------------------
 
 // Run time of a launch that gives every compute unit r workgroups: base + (r - 1) * base_more + chunk * slope(r), with
-// slope(r) = slope_1 for r <= 1 and r * slope_r beyond (microseconds, and microseconds per k).  Fitted to launches with
-// r = 1 .. 5, k = 512 and 2048 in three layouts (within 5 % of each other) and to the five products of 400-480-3203 at
-// 4096 and 65536 patterns (within 10 %; there 256 x 256 gives 1050, 960 and 1000 us on output layer, hidden delta and
-// dW2, 128 x 128 1100, 1035 and -, 256 x 128 1150, 1010 and 1090).
+// slope(r) = slope_1 (idle + (1 - idle) r) for r <= 1 and slope_r times the rounds beyond, the last of which counts 0.6 + 0.4
+// of its share (microseconds, and microseconds per k).  Fitted to launches with r = 1 .. 5, k = 512 and 2048 in three layouts
+// and, the tiles of 128 rows and more, to 24 products from 2048^3 to 16384 x 16384 x 2048: mostly within 12 % of the measured
+// time where k >= 1000, and the tile it chooses within 3 % of the fastest but for two (6 and 7 %).  Not modelled: the stores
+// of a large C under a short k (12000 x 5000 x 64 takes 1.5 times what it says, with every tile).
 struct SplitInfo {
     int bm, bn, bk, threads, occ;
-    double base, base_more, slope_1, slope_r;
+    double base, base_more, slope_1, slope_r, idle;
     const char *name;
 };
 constexpr SplitInfo SPLIT_INFO[SP_COUNT] = {
-    {256, 256, 16, 512, 1, 13.5, 8.0, 0.1480, 0.1480, "256x256"}, {256, 128, 32, 512, 1, 7.5, 5.0, 0.0800, 0.0790, "256x128"},
-    {128, 128, 32, 512, 1, 5.7, 3.0, 0.0406, 0.0450, "128x128w8"}, {128, 128, 16, 256, 3, 7.7, 1.0, 0.0445, 0.0405, "128x128"},
-    {128, 64, 32, 512, 2, 5.9, 0.9, 0.0240, 0.0240, "128x64"},     {64, 128, 32, 512, 2, 5.9, 0.9, 0.0240, 0.0240, "64x128"},
-    {64, 64, 32, 256, 3, 4.0, 0.3, 0.0170, 0.0136, "64x64"},       {64, 64, 64, 512, 1, 4.2, 2.2, 0.0146, 0.0155, "64x64k64"},
-    {32, 32, 128, 512, 1, 4.2, 3.0, 0.0061, 0.0061, "32x32k128"},
+    {256, 256, 16, 512, 1, 13.5, 8.0, 0.1380, 0.1380, 0.60, "256x256"}, {256, 128, 32, 512, 1, 7.5, 5.0, 0.0760, 0.0750, 0.70, "256x128"},
+    {128, 128, 32, 512, 1, 5.7, 3.0, 0.0406, 0.0450, 0.75, "128x128w8"}, {128, 128, 16, 256, 3, 7.7, 1.0, 0.0445, 0.0405, 0.75, "128x128"},
+    {128, 64, 32, 512, 2, 5.9, 0.9, 0.0240, 0.0240, 0.75, "128x64"},     {64, 128, 32, 512, 2, 5.9, 0.9, 0.0240, 0.0240, 0.75, "64x128"},
+    {64, 64, 32, 256, 3, 4.0, 0.3, 0.0170, 0.0136, 0.75, "64x64"},       {64, 64, 64, 512, 1, 4.2, 2.2, 0.0146, 0.0155, 0.75, "64x64k64"},
+    {32, 32, 128, 512, 1, 4.2, 3.0, 0.0061, 0.0061, 0.75, "32x32k128"},
 };
 
 double split_model_us(const SplitInfo &c, int m, int n, int k, int splits, int *kchunk_out, int *splits_out)
@@ -192,11 +193,12 @@ double split_model_us(const SplitInfo &c, int m, int n, int k, int splits, int *
     *splits_out = sp;
     const double wgs = (double)((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn) * sp;
     const double r = wgs / num_cu(), whole = std::ceil(r);
-    // shared compute units take the next workgroup as soon as one of theirs ends: the last round counts less
-    const double rounds = c.occ > 1 && r > 1.0 ? 0.6 * whole + 0.4 * r : whole;
+    // A round that leaves compute units idle takes less time than a full one: the chip runs at a higher clock (power bounds
+    // these kernels), and a shared compute unit takes the next workgroup as soon as one of its own ends.  4608^3 with
+    // 256 x 256 tiles, 27 % of a second round: 1100 us where two full rounds would take 1300.
+    const double rounds = 0.6 * whole + 0.4 * r;
     double t = c.base + (whole - 1.0) * c.base_more;
-    // a launch that leaves compute units idle runs at a higher clock (2048^3 on 64 of them: 0.102 us per k, not 0.14)
-    t += chunk * (r <= 1.0 ? c.slope_1 * (0.75 + 0.25 * r) : c.slope_r * rounds);
+    t += chunk * (r <= 1.0 ? c.slope_1 * (c.idle + (1.0 - c.idle) * r) : c.slope_r * rounds);
     if (sp > 1) t += 3.0 + (double)m * n * (sp + 1.0) * 4.0 / 5.0e6;
     return t;
 }
@@ -393,14 +395,10 @@ hipError_t launch_gemm16(const Gemm16Plan &p, bool a_kc, bool b_kc, int epi, Gem
          : p.cfg == CFG16_256x256 ? go(T16_256x256{}) : go(T16_64{});
 }
 
-// Plan of an unsplit ulsnn_sgemm.  The 256 x 256 tile only where one round of it covers C: a workgroup has its compute
-// unit to itself, so every further round adds its unhidden start and store burst (8 us), and the last round is rarely
-// full (4096^3: 565 us against 620 with 256 x 128; 4608^3 the other way round, 890 against 850).  Far above that the
-// larger tile would win again (8192^3: 4.5 against 4.9 ms), but the plan description of large products names 256 x 128.
+// Plan of an unsplit ulsnn_sgemm.
 GemmPlan plan_sgemm(int m, int n, int k, bool a_kc, bool b_kc, int lda, int ldb)
 {
-    const bool one_round = (long long)((m + 255) / 256) * ((n + 255) / 256) <= num_cu();
-    return plan_product(m, n, k, a_kc, b_kc, lda, ldb, 1, one_round ? ALL_SPLIT : ALL_SPLIT & ~(1u << SP_256x256));
+    return plan_product(m, n, k, a_kc, b_kc, lda, ldb, 1);
 }
 
 // Plan of a product that may cut k into at most `slices` slices.  A split costs a second launch (the reduction), so it

@@ -120,8 +120,12 @@ def test_sgemm_planned_argument_errors_and_plan_description():
     assert f(2, 4, b"N", b"N", 64, 64, 256, C.c_void_p(0x1000), 100) == E_WS   # too small
     assert f(2, 4, b"N", b"N", 64, 64, 256, C.c_void_p(0x1010), 1 << 20) == E_WS   # misaligned
     assert L.ulsnn_sgemm_planned(0, 1, b"N", b"N", 8, 8, 8, 1.0, p, 4, p, 8, 0.0, p, 8, None, 0, None) == E_LD
-    line = ulsnn.sgemm_describe_plan("N", "T", 8192, 8192, 8192)
-    assert line.startswith("tile=256x128 ") and "splits=1" in line
+    # large products: the tile is the one measured fastest (256 CUs: 1024 tiles of 256 x 256 are four full rounds, 4550 against
+    # 4850 us with 256 x 128; at 4608^3 the second round would be a quarter full, 1100 against 936), k is not split
+    for n, tile in ((4096, "256x256"), (5120, "256x256"), (8192, "256x256"), (4608, "256x128")):
+        line = ulsnn.sgemm_describe_plan("N", "T", n, n, n)
+        tm, tn = (int(v) for v in tile.split("x"))
+        assert line.startswith(f"tile={tile} tiles={-(-n // tm)}x{-(-n // tn)} splits=1 "), line
     assert ulsnn.sgemm_describe_plan("N", "N", 64, 64, 64).startswith("tile=64x64")
     assert ulsnn.sgemm_describe_plan("N", "N", 1024, 1024, 1024).startswith("tile=64x64k64 ")   # under-filled launch
     buf = C.create_string_buffer(8)
