@@ -193,16 +193,19 @@ def test_epoch_chunk_plans_against_the_oracle():
     """The kernels the 9,000,000-pattern epoch really runs, element by element against the oracle.
 
     Its last chunk has 87,104 patterns = one internal pass of 65536 (planned exactly like each of the four passes
-    of a 262144-pattern chunk: large tiles with the bias / tanh' epilogues inside the products, 160-row tiles and
-    long k splits for the weight gradients) + a pass of 21568 (another set of tile shapes).  The plan description
-    is checked first, so this test cannot drift off those plans unnoticed."""
+    of a 262144-pattern chunk: 256 x 256 tiles with the bias / tanh' epilogues inside the products and k splits for the
+    weight gradients) + a pass of 21568 (smaller tiles too, and a split hidden delta).  The plan of each of the five
+    products is checked first, so this test cannot drift off those plans unnoticed."""
     shape, n = si.MLP_JOCR, 87_104
     full = _plan_lines(ulsnn.mlp_grad_describe_plan(shape.n_in, shape.n_hid, shape.n_out, 262_144))
     last = _plan_lines(ulsnn.mlp_grad_describe_plan(shape.n_in, shape.n_hid, shape.n_out, n))
     assert "tail" not in full and last["pass"] == full["pass"], (full, last)
-    big_tiles = {"256x128", "128x128w8", "160x128"}
-    assert {t for t, _, _ in last["pass"].values()} & big_tiles and last["pass"]["dW2"][1] > 1
-    assert last["tail"] != last["pass"]
+    assert {name: plan[:2] for name, plan in last["pass"].items()} == {
+        "hidden_layer": ("256x256", 1), "output_layer": ("256x256", 1), "dW2": ("256x256", 19),
+        "hidden_delta": ("256x256", 1), "dW1": ("256x256", 64)}, last["pass"]
+    assert {name: plan[0] for name, plan in last["tail"].items()} == {
+        "hidden_layer": "128x128", "output_layer": "256x256", "dW2": "256x256", "hidden_delta": "256x256",
+        "dW1": "128x128w8"} and last["tail"]["hidden_delta"][1] > 1, last["tail"]
     print("pass of 65536:", last["pass"])
     print("pass of 21568:", last["tail"])
     p = _problem(shape, 2, n)
