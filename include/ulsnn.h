@@ -92,9 +92,11 @@ int ulsnn_sgemm_ws(char transa, char transb, int m, int n, int k, float alpha, c
  *                      product accumulates in fp32; the softmax statistics (row maximum, sum of exponentials, the
  *                      label's logit) and with them the loss are taken from the fp32 accumulators of the output
  *                      layer before its logits are rounded; dW1, dW2, db1, db2 (and b1, b2) stay fp32.
- *                      Fastest when n_in and n_hid are multiples of 8 (16-byte rows); other sizes are correct but
- *                      use an element-wise fetch for the operands whose rows are not 16-byte aligned (W1 and W2
- *                      are re-laid out internally, X is not).  Any other value: ULSNN_ERR_UNSUPPORTED.
+ *                      Fastest when n_in and n_hid are multiples of 8 (16-byte rows).  Operands whose rows are not
+ *                      16-byte aligned are copied into aligned rows inside the workspace: W1 and W2 always, X by a
+ *                      gradient from 128 patterns on and by an error alone where n_in > 64, if the workspace holds it
+ *                      beside the partial products (n_in up to about 16 n_hid); otherwise X is fetched element by
+ *                      element, with the same result.  Any other value: ULSNN_ERR_UNSUPPORTED.
  *   n_in, n_hid and n_out may not exceed ULSNN_MAX_LD (ULSNN_ERR_UNSUPPORTED).
  *   workspace: device scratch of at least ulsnn_mlp_grad_workspace_bytes(desc, batch) bytes, 256-byte aligned.
  *     Its contents on entry do not matter and are undefined on return.  Two calls that may run concurrently

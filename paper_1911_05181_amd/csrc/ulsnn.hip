@@ -822,12 +822,14 @@ int mlp_grad_impl16(const ulsnn_mlp_desc *d, const u16 *W1, const u16 *W2, const
         const float *ts = task.targets ? task.targets + (size_t)r0 * n_out : nullptr;
         // Patterns whose rows are not 16-byte aligned (n_in no multiple of 8) are copied into aligned rows too, in the upper
         // half of the partial region where they fit there: both products that read them would go element by element
-        // otherwise (533-106-290, 3034 patterns: hidden layer 37 us and dW1 18.5 without; 12.6, 5.8 and 5.6 for the copy
-        // with it; whole gradient 401-480-3203, 65536 patterns: 1319 us without, 1082 with).  Not below 65536 elements,
-        // where the launch costs what it saves (700 x 99 loss: 28.1 us without, 28.5 with; 300 x 33: 25.8 and 28.3).
+        // otherwise.  A gradient gains from 128 rows on, whatever the width, because its dW1 walks the rows (9-16-10, 300
+        // patterns: 45 -> 37 us; 33-64-40, 1000: 50 -> 38; 401-480-3203, 65536: 1319 -> 1082; with 50 rows nothing).  An error
+        // alone reads them once, n_in deep: up to two k steps (n_in <= 64) the launch costs what it saves or more (33-64-40,
+        // 1000 patterns: 13.8 -> 15.9, 57-128-100, 30000: 26.2 -> 28.0), beyond it gains (65-480-480, 5000: 29.2 -> 25.6;
+        // 401-128-64, 160: 32.6 -> 18.5).
         const int ldx_copy = (int)round_up((size_t)n_in, 8);
         const size_t half_pb = L.floats_pb / 2 / 64 * 64;      // floats, 256-byte aligned
-        const bool copy_x = !rows_16b_aligned(Xs, n_in) && (size_t)rows * n_in >= 65536 &&
+        const bool copy_x = !rows_16b_aligned(Xs, n_in) && (task.backward ? rows >= 128 : n_in > 64) &&
                             (size_t)rows * ldx_copy * sizeof(u16) <= half_pb * sizeof(float);
         const size_t floats_pb = copy_x ? half_pb : L.floats_pb;
         const Gemm16Plan p1 = plan_gemm16(rows, n_hid, n_in, true, false, false, 0);

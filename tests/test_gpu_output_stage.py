@@ -46,11 +46,12 @@ def test_output_stage(n_out, dense):
         assert (got.double() - want).norm() <= 1e-5 * want.norm()          # (a single class: both are zero)
 
 
-@pytest.mark.parametrize("n_in,n_hid,n_out,batch", [(33, 200, 40, 1986), (402, 64, 100, 300), (333, 70, 33, 1000), (33, 20, 40, 70), (777, 3, 5, 400)])
+@pytest.mark.parametrize("n_in,n_hid,n_out,batch", [(33, 200, 40, 1986), (402, 64, 100, 300), (333, 70, 33, 1000), (65, 20, 40, 127), (9, 20, 40, 128), (777, 3, 5, 400)])
 @pytest.mark.parametrize("dense", [False, True])
 def test_bf16_patterns_with_unaligned_rows(n_in, n_hid, n_out, batch, dense):
-    """Rows of X that are not 16-byte aligned are copied into aligned ones from 65536 elements on where the workspace
-    holds them (not in the last two shapes: too few, and much wider than its hidden layer); bf16 operands: 1e-2."""
+    """Rows of X that are not 16-byte aligned are copied into aligned ones, by a gradient from 128 rows on and by an error
+    alone above 64 columns, where the workspace holds them (not for the last shape, much wider than its hidden layer).  The
+    copy changes no sum: the loss is the same bits either way.  bf16 operands: 1e-2."""
     net = si.MlpShape(n_in, n_hid, n_out, True)
     W1, W2, _, _ = si.mlp_weights(net, 9, device=DEV)
     b1, b2 = si.random_biases(net, 9, device=DEV)
@@ -70,3 +71,5 @@ def test_bf16_patterns_with_unaligned_rows(n_in, n_hid, n_out, batch, dense):
     res = (ulsnn.mlp_grad_mse if dense else ulsnn.mlp_grad)(W1, W2, X, T if dense else y, b1, b2)
     for got, want in ((res.dW1, x.t().contiguous() @ dA), (res.dW2, H.t().contiguous() @ D)):
         assert ((got.double() - want).norm() / want.norm()).item() <= 1e-2
+    only = (ulsnn.mlp_mse if dense else ulsnn.mlp_loss)(W1, W2, X, T if dense else y, b1, b2)
+    assert torch.equal(only, res.loss)
