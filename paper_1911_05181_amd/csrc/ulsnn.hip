@@ -1199,7 +1199,11 @@ LsLayout ls_layout(const ulsnn_mlp_desc *d, int batch)
 }
 
 // Layout of the batched slopes inside the (otherwise idle) gradient workspace, and how many steps fit at once: 0 if not even
-// one does (a subset close to the whole batch of a wide network), then the slopes come from gradients.
+// one does (a subset close to the whole batch of a wide network), then the slopes come from gradients.  So they do where the
+// stacked product's extra work, 8 n_hid n_out flop per pattern against a gradient's 6 n_hid n_out + 4 n_in n_hid, outweighs
+// its fewer launches: above 15 GFLOP.  Whole searches over 20000 patterns, stacked and with gradients: 400-480-3203 (2.3
+// MFLOP per pattern) on a subset of 5500 10.7 and 11.5 ms, 6500 12.3 and 12.7, 8192 14.8 and 14.3; 64-256-4096 on 6500 9.0
+// and 9.1, 8192 10.9 and 9.8, 12000 15.3 and 13.2.  Networks of few classes do less work stacked, at any size.
 struct SlopeLayout {
     int rows, ldp, lda, ldu;
     int steps;
@@ -1214,6 +1218,7 @@ SlopeLayout slope_layout(const ulsnn_mlp_desc *d, int rows, size_t bytes)
     S.lda = (int)round_up(2 * (size_t)d->n_hid, 32);
     S.ldu = (int)round_up((size_t)d->n_out, 32);
     if (rows > SLAB_ROWS || d->n_hid > ULSNN_MAX_LD / 2) return S;
+    if ((double)rows * d->n_hid * (2.0 * d->n_out - 4.0 * d->n_in) > 15.0e9) return S;
     size_t off = 0;
     S.off_p = off; off += round_up((size_t)rows * S.ldp * 4, 256);
     S.off_q = off; off += round_up((size_t)rows * S.ldp * 4, 256);
