@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -15,7 +16,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libulsnn.so"
 _lib = None
-_fast = None      # the extension module _fast_call once load() has bound it to the library
+_fast = None      # the extension module _fast_call once load() has bound it to the library (None without one)
 
 
 class UlsnnError(RuntimeError):
@@ -123,9 +124,22 @@ def load():
 def _bind_fast_call(L):
     """Argument marshalling in native code (csrc/fast_call.cpp): each of its functions makes the same checks as the code
     below and returns the library's status, or None when an argument is not plainly right; the Python path then makes
-    the checks one by one and raises the precise error."""
+    the checks one by one and raises the precise error.  The extension reads torch's tensors and so belongs to the torch it
+    was built with; libulsnn.so does not.  Without an extension for this torch every call takes the Python path, with a
+    warning: the same kernels and results, up to 10 us more per call."""
     global _fast
-    from . import _fast_call
+    why = None
+    try:
+        from . import _fast_call
+        built_for = getattr(_fast_call, "torch_version", "of another version")
+        if built_for != str(torch.__version__):
+            why = f"built with torch {built_for}, this is {torch.__version__}"
+    except ImportError as e:
+        why = str(e)
+    if why is not None:
+        warnings.warn(f"paper_1911_05181_amd: native argument checks not available ({why}); calls take the slower Python "
+                      "path.  Build again with `python -m paper_1911_05181_amd.build`.", RuntimeWarning, stacklevel=3)
+        return
     _fast_call.bind(*(C.cast(getattr(L, name), C.c_void_p).value for name in (
         "ulsnn_sgemm", "ulsnn_sgemm_ws", "ulsnn_mlp_grad", "ulsnn_mlp_grad_mse", "ulsnn_mlp_loss", "ulsnn_mlp_mse",
         "ulsnn_mlp_grad_epoch", "ulsnn_cg_direction", "ulsnn_dot", "ulsnn_axpy")))

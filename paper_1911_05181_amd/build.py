@@ -25,7 +25,8 @@ def fast_call_command():
     from torch.utils.cpp_extension import include_paths, library_paths
 
     return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+             f'-DBUILT_WITH_TORCH="{torch.__version__}"']
             + [f"-isystem{d}" for d in include_paths()] + ["-I" + sysconfig.get_paths()["include"]]
             + ["-o", FAST_CALL, os.path.join(CSRC, "fast_call.cpp")]
             + [f"-L{d}" for d in library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10"])

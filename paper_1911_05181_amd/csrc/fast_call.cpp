@@ -293,4 +293,13 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fast_call", nullptr, -1, methods}
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fast_call(void) { return PyModule_Create(&module); }
+// torch_version: the torch whose tensors this file was compiled to read; the binding uses the module with no other.
+PyMODINIT_FUNC PyInit__fast_call(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", BUILT_WITH_TORCH) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

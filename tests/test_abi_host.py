@@ -3,8 +3,11 @@ validation (which runs before any HIP call) returns the documented status codes.
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
+import torch
 
 import paper_1911_05181_amd as ulsnn
 from paper_1911_05181_amd.binding import _MlpDesc
@@ -398,3 +401,29 @@ def test_sgemm_ws_plan_splits_only_where_it_pays():
     assert L.ulsnn_sgemm_ws_describe_plan(b"N", b"N", 8, 8, 8, 0, None, 8) == 1      # null buffer
     assert L.ulsnn_sgemm_ws_describe_plan(b"X", b"N", 8, 8, 8, 0, buf, 64) == 2      # bad trans
     assert L.ulsnn_sgemm_ws_describe_plan(b"N", b"N", 0, 8, 8, 0, buf, 64) == 3      # bad dimension
+
+
+def test_binding_without_an_extension_for_this_torch():
+    """The argument-marshalling extension belongs to one torch, the library to none: without the extension, or with one
+    built for another torch, the binding loads with a warning and every call takes the Python path."""
+    code = """
+import sys, types, warnings
+if sys.argv[1] == "missing":
+    sys.modules["paper_1911_05181_amd._fast_call"] = None              # import raises ImportError
+else:
+    other = types.ModuleType("paper_1911_05181_amd._fast_call")
+    other.torch_version, other.bind = "0.0.1", None                    # never called
+    sys.modules["paper_1911_05181_amd._fast_call"] = other
+import paper_1911_05181_amd as ulsnn
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    assert ulsnn.version() > 0 and ulsnn.binding._fast is None
+    assert "paper_1911_05181_amd" in str([w for w in seen if w.category is RuntimeWarning][0].message)
+    ulsnn.load()
+    assert len([w for w in seen if w.category is RuntimeWarning]) == 1     # once
+print("ok")
+"""
+    for how in ("missing", "other"):
+        r = subprocess.run([sys.executable, "-c", code, how], cwd=ROOT, capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr
+    assert ulsnn.load() is not None and ulsnn.binding._fast.torch_version == str(torch.__version__)
