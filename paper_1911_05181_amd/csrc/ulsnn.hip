@@ -1466,13 +1466,14 @@ int ulsnn_mlp_grad_describe_plan(const ulsnn_mlp_desc *desc, int batch, char *bu
                          g[i]->est_us));
     };
     const SlabPlans P = plan_slab(L, desc->n_in, desc->n_hid, desc->n_out, L.slab);
-    add(snprintf(buf, buf_bytes, "rows_per_pass=%d workspace_bytes=%zu small_network_path=%d\n",
+    // (paired_backward: hidden delta and dW2 in one launch, which no plan does any more; the field stays for its readers)
+    add(snprintf(buf, buf_bytes, "rows_per_pass=%d paired_backward=0 workspace_bytes=%zu small_network_path=%d\n",
                  L.slab, L.bytes, (int)small_net_shape(desc, batch)));
     five_lines(P);
     const int tail = batch % L.slab;
     if (tail != 0 && used + 1 < buf_bytes) {
         const SlabPlans T = plan_slab(L, desc->n_in, desc->n_hid, desc->n_out, tail);
-        add(snprintf(buf + used, buf_bytes - used, "tail_rows=%d\n", tail));
+        add(snprintf(buf + used, buf_bytes - used, "tail_rows=%d paired_backward=0\n", tail));
         five_lines(T);
     }
     return ULSNN_OK;

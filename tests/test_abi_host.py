@@ -300,6 +300,9 @@ def test_plan_description_lists_the_shorter_last_pass():
     lines = text.strip().splitlines()
     assert lines[0].startswith("rows_per_pass=65536") and len(lines) == 12
     assert lines[6].startswith("tail_rows=21568")
+    # the sections' fields, in this order
+    assert [f.split("=")[0] for f in lines[0].split()] == ["rows_per_pass", "paired_backward", "workspace_bytes", "small_network_path"]
+    assert lines[6].split() == ["tail_rows=21568", "paired_backward=0"]
     assert [l.split(":")[0] for l in lines[7:]] == ["hidden_layer", "output_layer", "dW2", "hidden_delta", "dW1"]
     # a whole number of passes has no tail section, and its first pass is planned like any 65536-row pass
     whole = ulsnn.mlp_grad_describe_plan(400, 480, 3203, 262144).strip().splitlines()
