@@ -240,12 +240,19 @@ hipError_t launch_plan(const GemmPlan &p, bool a_kc, bool b_kc, int epi, GemmArg
     return p.split ? launch_split(p.cfg, p.splits, a_kc, b_kc, epi, a, s) : launch_fp32(p.cfg, p.splits, a_kc, b_kc, epi, a, s);
 }
 
+// Longest k that one workgroup sums through the split.  Its downward rounding grows with k (1.1e-11 k of the result) where
+// the other errors grow with the root: at 300,000 the split's error is 5.4e-6 and the fp32 instruction's 7.0e-6, at 2^21
+// 2.5e-5 and 1.8e-5; they cross near 800,000.
+constexpr int SPLIT_MAX_CHUNK = 1 << 19;
+
 // The plan of a product with the given leading dimensions.  The fp32 instruction serves rows so far apart that a tile
-// does not fit the buffer instructions' 32-bit offsets (and ulsnn_sgemm_planned, which names its tile shapes).
+// does not fit the buffer instructions' 32-bit offsets and sums longer than SPLIT_MAX_CHUNK (and ulsnn_sgemm_planned, which
+// names its tile shapes).
 GemmPlan plan_product(int m, int n, int k, bool a_kc, bool b_kc, int lda, int ldb, int split_limit, unsigned mask = ALL_SPLIT)
 {
     if (std::max(lda, ldb) > SPLIT_MAX_LD) return plan_gemm(m, n, k, a_kc, b_kc, split_limit, ALL_CFGS);
-    return plan_split(m, n, k, split_limit, mask);
+    const GemmPlan p = plan_split(m, n, k, split_limit, mask);
+    return p.kchunk <= SPLIT_MAX_CHUNK ? p : plan_gemm(m, n, k, a_kc, b_kc, split_limit, ALL_CFGS);
 }
 
 inline unsigned grid_for(size_t elems)
