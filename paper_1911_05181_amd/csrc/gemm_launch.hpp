@@ -18,9 +18,10 @@ enum SplitId { SP_256x256 = 0, SP_256x128, SP_128W8, SP_128, SP_128x64, SP_64x12
 constexpr int SPLIT_MAX_LD = (1 << 21) - 64;
 
 // One product: grid (tiles, k splits); a.tiles_m, a.tiles_n and a.kchunk are set.  Which layouts exist for an epilogue:
-// EPI_AXPBY and EPI_PARTIAL all four, EPI_BIAS_TANH and EPI_BIAS NN, EPI_TANHGRAD NT.
+// EPI_AXPBY and EPI_PARTIAL all four, EPI_BIAS_TANH and EPI_BIAS NN, EPI_TANHGRAD NT.  `mixed` (gemm_split.hpp): EPI_PARTIAL NT
+// and EPI_TANHGRAD, which has no other form.
 #define ULSNN_HIDDEN __attribute__((visibility("hidden")))
 ULSNN_HIDDEN hipError_t launch_fp32(int cfg, int splits, bool a_kc, bool b_kc, int epi, const GemmArgs &a, hipStream_t s);
-ULSNN_HIDDEN hipError_t launch_split(int cfg, int splits, bool a_kc, bool b_kc, int epi, const GemmArgs &a, hipStream_t s);
+ULSNN_HIDDEN hipError_t launch_split(int cfg, int splits, bool a_kc, bool b_kc, int epi, bool mixed, const GemmArgs &a, hipStream_t s);
 
 }  // namespace ulsnn

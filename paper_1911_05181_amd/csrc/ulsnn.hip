@@ -232,12 +232,12 @@ constexpr unsigned ALL_SPLIT = (1u << SP_COUNT) - 1;
 inline const char *plan_name(const GemmPlan &p) { return p.split ? SPLIT_INFO[p.cfg].name : CFG_INFO[p.cfg].name; }
 
 // Launch a product by its plan (either unit).
-hipError_t launch_plan(const GemmPlan &p, bool a_kc, bool b_kc, int epi, GemmArgs a, hipStream_t s)
+hipError_t launch_plan(const GemmPlan &p, bool a_kc, bool b_kc, int epi, GemmArgs a, hipStream_t s, bool mixed = false)
 {
     a.tiles_m = p.tiles_m;
     a.tiles_n = p.tiles_n;
     a.kchunk = p.kchunk;
-    return p.split ? launch_split(p.cfg, p.splits, a_kc, b_kc, epi, a, s) : launch_fp32(p.cfg, p.splits, a_kc, b_kc, epi, a, s);
+    return p.split ? launch_split(p.cfg, p.splits, a_kc, b_kc, epi, mixed, a, s) : launch_fp32(p.cfg, p.splits, a_kc, b_kc, epi, a, s);
 }
 
 // Longest k that one workgroup sums through the split.  Its downward rounding grows with k (1.1e-11 k of the result) where
@@ -737,7 +737,7 @@ int mlp_grad_impl(const ulsnn_mlp_desc *d, const void *W1v, const void *W2v, con
             GemmArgs p3 = a3, p4 = a4;
             if (P.g4.splits > 1) { p4.C = part_b; p4.partial_stride = (size_t)a4.M * a4.N; }
             if (P.g3.splits > 1) { p3.C = part_a; p3.partial_stride = (size_t)a3.M * a3.N; }
-            HIP_TRY(launch_plan(P.g4, true, true, P.g4.splits > 1 ? EPI_PARTIAL : EPI_TANHGRAD, p4, s));
+            HIP_TRY(launch_plan(P.g4, true, true, P.g4.splits > 1 ? EPI_PARTIAL : EPI_TANHGRAD, p4, s, true));   // (summed over patterns)
             HIP_TRY(launch_plan(P.g3, false, false, P.g3.splits > 1 ? EPI_PARTIAL : EPI_AXPBY, p3, s));
         }
         MARK(4);
