@@ -169,7 +169,7 @@ constexpr unsigned ALL_CFGS = (1u << CFG_COUNT) - 1;
 // Run time of a launch that gives every compute unit r workgroups: base + (r - 1) * base_more + chunk * slope(r), with
 // slope(r) = slope_1 (idle + (1 - idle) r) for r <= 1 and slope_r times the rounds beyond, the last of which counts 0.6 + 0.4
 // of its share (microseconds, and microseconds per k).  Fitted to launches with r = 1 .. 5, k = 512 and 2048 in three layouts
-// and, the tiles of 128 rows and more, to 24 products from 2048^3 to 16384 x 16384 x 2048: mostly within 12 % of the measured
+// and, the tiles of 128 rows and more, to 29 products from 2048^3 to 16384 x 16384 x 2048: mostly within 12 % of the measured
 // time where k >= 1000, and the tile it chooses within 3 % of the fastest but for two (6 and 7 %).  Not modelled: the stores
 // of a large C under a short k (12000 x 5000 x 64 takes 1.5 times what it says, with every tile).
 struct SplitInfo {
@@ -410,8 +410,9 @@ GemmPlan plan_sgemm(int m, int n, int k, bool a_kc, bool b_kc, int lda, int ldb)
 
 // Plan of a product that may cut k into at most `slices` slices.  A split costs a second launch (the reduction), so it
 // is taken where it beats the unsplit tiles of 64 rows and more.  The 32 x 32 tile, which splits k over the wavefronts
-// of a workgroup instead, is preferred to it only where it is clearly better (0.7: below 512^3, where it takes 7.4 us
-// and a split 9 to 10; with more k or less of C the split overtakes it).
+// of a workgroup instead, is preferred to it up to 0.92 of its modelled time: over 48 products of 64 x 64 to 640 x 640 and
+// k = 512 to 4096 that is where the measured times cross (512^3 7.3 us, 9.3 split; 256 x 256 x 768 8.6 and 9.0, x 1024
+// 10.1 and 8.8; 512 x 512 x 1536 13.4 and 13.0).
 GemmPlan plan_sgemm_ws(int m, int n, int k, bool a_kc, bool b_kc, int lda, int ldb, size_t slices)
 {
     const GemmPlan one = plan_sgemm(m, n, k, a_kc, b_kc, lda, ldb);
@@ -422,7 +423,7 @@ GemmPlan plan_sgemm_ws(int m, int n, int k, bool a_kc, bool b_kc, int lda, int l
         return (cut.splits > 1 && cut.est_us < 0.8 * one.est_us) ? cut : one;
     }
     const GemmPlan cut = plan_product(m, n, k, a_kc, b_kc, lda, ldb, limit, ALL_SPLIT & ~(1u << SP_32K128));
-    return (cut.splits > 1 && one.est_us > 0.7 * cut.est_us) ? cut : one;
+    return (cut.splits > 1 && one.est_us > 0.92 * cut.est_us) ? cut : one;
 }
 
 // ---------------------------------------------------------------------------------------------------------
