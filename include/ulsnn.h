@@ -51,7 +51,11 @@ typedef enum ulsnn_status {
  *   Reference-BLAS rules: m == 0 or n == 0 returns ULSNN_OK and touches nothing; k == 0 or alpha == 0 gives
  *   C = beta*C; with beta == 0, C is written WITHOUT being read (NaN or Inf already in C do not propagate).
  *   Only the m x n entries of C are written; padding columns (n .. ldc-1) are left as they are.
- *   Products are accumulated in fp32 on the matrix cores; the order of summation is unspecified.
+ *   Products are accumulated in fp32 on the matrix cores; the order of summation is unspecified.  The same call gives
+ *   the same bits, but the last bits of an element may depend on its place: equal rows of op(A) (or equal columns of
+ *   op(B)) need not give equal bits in C.  Operands keep all 24 bits, denormals included; sub-tiles of C whose row or
+ *   column holds an infinity or a NaN, an operand above 2^112 or a sum above 2^96 are computed a second time by a slower
+ *   kernel (up to four times the time of the call if all of C is such).
  *   A, B read-only; pointers need only 4-byte alignment.  A or B NULL is an error unless that operand is
  *   never read (m, n == 0, or k == 0, or alpha == 0).
  *   lda and ldb may not exceed ULSNN_MAX_LD (the kernels keep 32-bit element offsets inside a tile of up to 256
@@ -230,7 +234,7 @@ int ulsnn_mlp_grad_timed(const ulsnn_mlp_desc *desc, const void *W1, const void 
  * for `batch` patterns: for the first internal pass if the batch is processed in several, followed, when the last
  * pass is shorter, by a line "tail_rows=R" and the five lines of that pass.  The first line also
  * says whether the call would take the two-launch path for small networks instead (small_network_path=1: nets up
- * to 128-64-64 at up to 4096 patterns, softmax form, fp32).  Launches nothing.
+ * to 128-64-64 at up to 4096 patterns, fp32).  Launches nothing.
  */
 int ulsnn_mlp_grad_describe_plan(const ulsnn_mlp_desc *desc, int batch, char *buf, size_t buf_bytes);
 
@@ -272,7 +276,8 @@ int ulsnn_cg_direction(int64_t n, const float *g_new, const float *g_old, float 
  * synchronises hip_stream once per group of bracketing steps (groups of 2, 4, 8, 8, ... steps; all steps of a group
  * are evaluated, also those after
  * the one that closes the bracket: spare slopes on the small subset instead of a round trip each) and once at the
- * end; slopes are directional derivatives, taken without forming the gradient where the workspace holds a step's rows; the vertex of the parabola, the comparison of the errors and the weight update use steps computed on the
+ * end; slopes are directional derivatives, taken without forming the gradient where the workspace
+ * holds a step's rows and that is less work; the vertex of the parabola, the comparison of the errors and the weight update use steps computed on the
  * device (when the parabola is not convex the midpoint is evaluated a second time in the vertex's place).  The
  * evaluation counts in `result` are the algorithm's own (what a sequential search would have evaluated).
  * desc->workspace must hold ulsnn_mlp_line_search_workspace_bytes(desc, batch) bytes (the gradient
@@ -292,8 +297,10 @@ int ulsnn_mlp_line_search(const ulsnn_mlp_desc *desc, float *W1, float *W2, cons
                           int max_doublings, ulsnn_line_search_result *result);
 
 /*
- * The same operation as ulsnn_sgemm (section 3.1) with the blocking chosen by the caller instead of the built-in
- * planner (for autotuning, and for tests that must reach every tile shape): `tile_shape` is one of
+ * The same operation as ulsnn_sgemm (section 3.1) on the fp32 matrix instruction, with the blocking chosen by the caller
+ * (for tests that must reach every tile shape, and as a reference for accuracy and speed).  ulsnn_sgemm itself uses other
+ * kernels with tile shapes of their own, up to twice as fast, except for leading dimensions above 2^21 - 64 and unsplit sums
+ * above k = 2^19: a search over these shapes does not find its best.  `tile_shape` is one of
  * ULSNN_TILE_*, `k_splits` >= 1 the number of slices the k range is cut into (slices are rounded up to the k
  * step of the tile shape, 16 or 64, so fewer may remain).  With more than one slice the partial products go to `workspace` (device
  * memory, 256-byte aligned, at least k_splits*m*n*4 bytes; else ULSNN_ERR_WORKSPACE) and are added in slice
