@@ -20,10 +20,25 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include <type_traits>
+#include <utility>
+
 namespace ulsnn {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// f(integral_constant<0>) ... f(integral_constant<N - 1>)
+template <class F, int... I>
+__device__ __forceinline__ void call_with(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void for_each_index(F &&f)
+{
+    call_with(f, std::make_integer_sequence<int, N>{});
+}
 
 enum Epilogue {
     EPI_AXPBY = 0,      // C = alpha*acc + beta*C   (beta == 0: C not read)

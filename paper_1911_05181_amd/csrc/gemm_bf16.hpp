@@ -262,17 +262,28 @@ __device__ __forceinline__ void softmax_merge(float &m, float &s, float om, floa
     m = nm;
 }
 
+constexpr int EPILOGUE_SCRATCH_ROW = 36, EPILOGUE_SCRATCH_FLOATS = 32 * EPILOGUE_SCRATCH_ROW;
+// A 32 x 32 block of 16 x 16 accumulators (of swapped operands: a lane holds row lane%16, four consecutive columns from
+// 4*(lane/16)) into the scratch.
+template <int RM, int RN>
+__device__ __forceinline__ void block_to_scratch(float *scr, const floatx4 (&acc)[RM][RN], const int x, const int y, const int lane)
+{
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+            *reinterpret_cast<floatx4 *>(scr + (a * 16 + (lane & 15)) * EPILOGUE_SCRATCH_ROW + b * 16 + (lane >> 4) * 4) = acc[2 * x + a][2 * y + b];
+}
 // Epilogue of one tile: the accumulators of this wavefront's sub-tile (rows i0 + wrow.., columns j0 + wcol..) leave
 // through `scratch`, EPILOGUE_SCRATCH_FLOATS floats of LDS private to the wavefront, wherever rows of C are 16-byte
 // aligned.  Every thread of the workgroup must call this (it starts with a workgroup barrier: the operand panels,
 // whose LDS the scratch may reuse, are dead after it).
-constexpr int EPILOGUE_SCRATCH_FLOATS = 32 * 36;
-template <class Cfg, int EPI>
-__device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, floatx16 (&acc)[Cfg::TM][Cfg::TN],
-                                                float *scratch, const int i0, const int j0, const int z,
-                                                const int tile_n)
+template <class Cfg, int EPI, class Acc>
+__device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, Acc &acc, float *scratch, const int i0, const int j0,
+                                                const int z, const int tile_n)
 {
     constexpr int TM = Cfg::TM, TN = Cfg::TN;
+    constexpr bool WIDE = Cfg::BK == 64;      // (launched only where bf16 rows of C are 16-byte aligned)
     constexpr bool OUT_BF16 = (EPI == EPI_BIAS_TANH || EPI == EPI_TANHGRAD || EPI == EPI_BIAS_STATS || EPI == EPI_TANH_MSE);
     constexpr bool MSE = (EPI == EPI_TANH_MSE || EPI == EPI_MSE_ONLY);
     constexpr bool STATS = (EPI == EPI_BIAS_STATS || EPI == EPI_STATS_ONLY || MSE);
@@ -300,7 +311,7 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, floatx16 (&
         // wavefront's sub-tile, so the row's running (max, sum of exp) stays in registers across y and is joined
         // over the 4 lanes that share the row with two shuffles.  C (bf16, 16-byte aligned rows: the caller's
         // workspace) is written unless only the statistics are wanted.
-        constexpr int SLD = 36;
+        constexpr int SLD = EPILOGUE_SCRATCH_ROW;
         __syncthreads();
         float *scr = scratch;
         const int srow = lane >> 2, scol = (lane & 3) * 8;
@@ -316,8 +327,12 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, floatx16 (&
             }
 #pragma unroll
             for (int y = 0; y < TN; ++y) {
+                if constexpr (WIDE) {
+                    block_to_scratch(scr, acc, x, y, lane);
+                } else {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) scr[(8 * (r / 4) + 4 * h + (r % 4)) * SLD + l32] = acc[x][y][r];
+                    for (int r = 0; r < 16; ++r) scr[(8 * (r / 4) + 4 * h + (r % 4)) * SLD + l32] = acc[x][y][r];
+                }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -419,8 +434,10 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, floatx16 (&
         return;
     }
     const bool rows_vec = (EPI == EPI_PARTIAL) ? ((g.N & 3) == 0 && (g.partial_stride & 3) == 0 && g.c_vec) : g.c_vec != 0;
-    if (rows_vec) {
-        constexpr int SLD = 36;                                   // scratch row stride (floats): 16-byte aligned rows
+    if (WIDE || rows_vec) {
+        typedef floatx4 floatx4_a4 __attribute__((aligned(4)));
+        using floatx4_store = std::conditional_t<WIDE, floatx4_a4, floatx4>;
+        constexpr int SLD = EPILOGUE_SCRATCH_ROW;
         __syncthreads();                                          // every wavefront is done reading the panels
         float *scr = scratch;
         const int srow = lane >> 2, scol = (lane & 3) * 8;        // this lane's row (of 16 per pass) and 8 columns
@@ -428,8 +445,12 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, floatx16 (&
         for (int x = 0; x < TM; ++x) {
 #pragma unroll
             for (int y = 0; y < TN; ++y) {
+                if constexpr (WIDE) {
+                    block_to_scratch(scr, acc, x, y, lane);
+                } else {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) scr[(8 * (r / 4) + 4 * h + (r % 4)) * SLD + l32] = acc[x][y][r];
+                    for (int r = 0; r < 16; ++r) scr[(8 * (r / 4) + 4 * h + (r % 4)) * SLD + l32] = acc[x][y][r];
+                }
                 // LDS operations of one wavefront complete in order; the fences keep the compiler from moving the
                 // reads of other lanes' elements above these writes (and the next block's writes above the reads)
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -490,8 +511,8 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, floatx16 (&
                             }
                         }
                         if (whole) {
-                            *reinterpret_cast<floatx4 *>(Cf + at) = floatx4{v[0], v[1], v[2], v[3]};
-                            *reinterpret_cast<floatx4 *>(Cf + at + 4) = floatx4{v[4], v[5], v[6], v[7]};
+                            *reinterpret_cast<floatx4_store *>(Cf + at) = floatx4{v[0], v[1], v[2], v[3]};
+                            *reinterpret_cast<floatx4_store *>(Cf + at + 4) = floatx4{v[4], v[5], v[6], v[7]};
                         } else {
 #pragma unroll
                             for (int e = 0; e < 8; ++e)
@@ -503,6 +524,7 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, floatx16 (&
         }
         return;
     }
+    if constexpr (!WIDE) {
 #pragma unroll
     for (int y = 0; y < TN; ++y) {
         const int j = j0 + wcol + y * 32 + l32;
@@ -534,6 +556,9 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args &g, floatx16 (&
             }
         }
     }
+    }
+    (void)l32;
+    (void)h;
     (void)OUT_BF16;
 }
 
@@ -811,6 +836,322 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void gemm16_kern
 {
     __shared__ __attribute__((aligned(16))) u16 lds[gemm16_lds_elems<Cfg, A_KC, B_KC>()];
     gemm16_tile<Cfg, A_KC, B_KC, EPI, DELTA>(g, blockIdx.y * gridDim.x + blockIdx.x, gridDim.y, lds);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// The large tile of the long products: 256 x 256 by eight wavefronts, one workgroup per CU, steps of 64 k.
+//
+// Per step a wavefront issues 64 instructions of 16 x 16 x 32 (the 32 x 32 x 16 form reaches a tenth less: power), 0.95 us of
+// matrix time per step; the fragments' LDS reads take 0.7 us and the panels' writes 0.25 us beside them, so what the step costs
+// beyond that is latency, and the loop is laid out to hide it:
+//   * one set of staging registers: a vector goes to the other LDS stage between the products of two fragments and the same
+//     vector of the step after next is requested at once, so every load has a whole step to arrive (a second set found no
+//     registers: 227 of 256 are in use, 249 where the delta is formed);
+//   * the barrier stands before the last fragment's products, which cover the next step's first LDS reads;
+//   * the partial step, if any, is the first and is fetched apart; the rest is ONE loop body without branches around loads
+//     (loads beyond the last step go to an empty buffer and read as zero).
+// Against the tile it took the place of (32 k per step, two register sets, 32 x 32 x 16): 4096^3 NT 136 -> 115 us (1.20 PFLOP/s),
+// TN 134 -> 118; at 65536 patterns of 400-480-3203 (1.7 % of k is padding, 6 % of the rows) the hidden delta 282 -> 237 us,
+// without forming the delta 255 -> 214; dW2 286 -> 249, without 245 -> 203; dW1 44 -> 39.  The gradient: 1019 -> 930 us, of
+// 1024-1024-4096 at 20000 patterns 834 -> 700.  At k = 480 (output layer) it gives 362 against 372 us for the 128 x 128 tile at
+// 65536 patterns and loses at 10000 (87 against 80): its stores wait for nothing to overlap with, so short k keeps that one.
+// ---------------------------------------------------------------------------------------------------------
+
+template <int BM_, int BN_, int WM_, int WN_, int WAVES_PER_SIMD_>
+struct Wide16 {
+    static constexpr int BM = BM_, BN = BN_, BK = 64, WM = WM_, WN = WN_, WAVES_PER_SIMD = WAVES_PER_SIMD_;
+    static constexpr int THREADS = WM * WN * 64;
+    static constexpr int WTM = BM / WM, WTN = BN / WN;
+    static constexpr int TM = WTM / 32, TN = WTN / 32;
+    static_assert(WTM % 32 == 0 && WTN % 32 == 0, "tile shape");
+};
+
+// One operand's panel of 64 k in LDS.  KC: rows of eight 16-byte chunks, chunk c of row r at position c ^ r%8, so that both the
+// eight lanes that fill a row and the eight rows a fragment read touches at a time cover all banks.  MC: k rows as they arrive,
+// for the transpose read (see Panel16).
+template <bool KC, int R, int THREADS>
+struct WidePart {
+    static constexpr int LD = KC ? 64 : R + 16, SIZE = KC ? R * 64 : 64 * LD;
+    static constexpr int NV = R * 8 / THREADS;                               // 16-byte vectors per thread and step
+    static constexpr int PER_ROW = KC ? 8 : R / 8, ROWS = THREADS / PER_ROW;      // vector v: memory row tid / PER_ROW + v * ROWS
+    static_assert(R * 8 % THREADS == 0 && THREADS % PER_ROW == 0, "every thread owns whole vectors, at one column");
+    u16x8 reg[NV];
+    unsigned off;           // bytes
+    int lds0;
+
+    __device__ __forceinline__ static int row(const int tid, const int v) { return tid / PER_ROW + v * ROWS; }
+    __device__ __forceinline__ static int col(const int tid) { return tid % PER_ROW * 8; }
+    __device__ __forceinline__ void init(const int ld, const int valid, const int tid)
+    {
+        off = ((unsigned)row(tid, 0) * (unsigned)ld + (unsigned)col(tid)) * 2u;
+        if (!KC && col(tid) >= valid) off = 0x80000000u;      // a vector beyond the matrix: reads as zero
+        lds0 = KC ? row(tid, 0) * 64 + ((tid % 8) ^ (row(tid, 0) % 8)) * 8 : row(tid, 0) * LD + col(tid);
+        static_assert(!KC || ROWS % 8 == 0, "the position of a chunk is the same for every vector");
+    }
+    // bytes of a full step's panel from its first element
+    __device__ __forceinline__ static int records(const int ld, const int valid)
+    {
+        const int n = valid < R ? valid : R;
+        return KC ? ((n - 1) * ld + 64) * 2 : (63 * ld + (n + 7) / 8 * 8) * 2;
+    }
+    template <int V>
+    __device__ __forceinline__ void fetch(const __amdgpu_buffer_rsrc_t rs, const int ld)
+    {
+        reg[V] = __builtin_bit_cast(u16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, off + (unsigned)(V * ROWS * 2) * (unsigned)ld, 0, 0));
+    }
+    // the step of `left` < 64 k at `p`: `fill` beyond them
+    __device__ __forceinline__ void fetch_partial(const u16 *p, const int ld, const int valid, const int left, const int tid, const u16 fill = 0)
+    {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int r = row(tid, v), c = col(tid), n = KC ? left - c : r < left ? 8 : 0;      // valid elements
+            u16x8 val = {fill, fill, fill, fill, fill, fill, fill, fill};
+            if (n > 0 && (KC ? r : c) < valid) {
+                val = load8_aligned(p + (size_t)r * ld + c);      // (its first element is inside, so the 16 bytes are readable)
+#pragma unroll
+                for (int e = 1; e < 8; ++e) val[e] = e < n ? val[e] : fill;
+            }
+            reg[v] = val;
+        }
+    }
+    template <int V>
+    __device__ __forceinline__ void store(u16 *lds) const
+    {
+        *reinterpret_cast<u16x8 *>(lds + lds0 + V * ROWS * LD) = reg[V];
+    }
+    // where this lane's elements of a fragment lie: row (KC) or transposed (MC), k half t
+    __device__ __forceinline__ static int fragment(const int row0, const int lane, const int t)
+    {
+        if (KC) return (row0 + (lane & 15)) * 64 + ((t * 4 + (lane >> 4)) ^ (lane & 7)) * 8;
+        return (t * 32 + (lane >> 4) * 8 + ((lane & 15) >> 2)) * LD + row0 + 4 * (lane & 3);
+    }
+    __device__ __forceinline__ static bf16x8 read(const u16 *p, const int block)
+    {
+        if (KC) return *reinterpret_cast<const bf16x8 *>(p + block * 16 * 64);
+        typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(p + block * 16));
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(p + block * 16 + 4 * LD));
+        typedef short shortx8 __attribute__((ext_vector_type(8)));
+        return __builtin_bit_cast(bf16x8, shortx8{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w});
+    }
+};
+
+template <class Cfg, bool A_KC, bool B_KC>
+constexpr int wide16_stage()
+{
+    return WidePart<A_KC, Cfg::BM, Cfg::THREADS>::SIZE + WidePart<B_KC, Cfg::BN, Cfg::THREADS>::SIZE;
+}
+
+template <class Cfg, bool A_KC, bool B_KC, int EPI, int DELTA>
+__device__ __forceinline__ void wide16_tile(const Gemm16Args &g, const int hw, const int splits, u16 *lds)
+{
+    constexpr bool DELTA_A = DELTA == 1, DELTA_B = DELTA == 2;
+    static_assert(!DELTA_A || A_KC, "the delta is formed on a k-contiguous A operand ...");
+    static_assert(!DELTA_B || !B_KC, "... or on an m-contiguous B operand");
+    constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = 64, THREADS = Cfg::THREADS;
+    constexpr int RM = Cfg::WTM / 16, RN = Cfg::WTN / 16;
+    using PA = WidePart<A_KC, BM, THREADS>;
+    using PB = WidePart<B_KC, BN, THREADS>;
+    constexpr int NA = PA::NV, NB = PB::NV, NU = NA + NB, B0 = PA::SIZE, STAGE = PA::SIZE + PB::SIZE;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wrow = wave / Cfg::WN * Cfg::WTM, wcol = wave % Cfg::WN * Cfg::WTN;
+    int tile_m, tile_n, z;
+    work_of_workgroup(hw, g.tiles_m, g.tiles_n, splits, tile_m, tile_n, z);
+    const int i0 = tile_m * BM, j0 = tile_n * BN;
+    const int kbeg = z * g.kchunk, kend = (kbeg + g.kchunk < g.K) ? kbeg + g.kchunk : g.K;
+    const int nfull = (kend - kbeg) / BK, left = (kend - kbeg) % BK, steps = nfull + (left > 0);
+
+    floatx4 acc[RM][RN];
+#pragma unroll
+    for (int a = 0; a < RM; ++a)
+#pragma unroll
+        for (int b = 0; b < RN; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    PA pa;
+    PB pb;
+    pa.init(g.lda, g.M - i0, tid);
+    pb.init(g.ldb, g.N - j0, tid);
+    const size_t step_a = A_KC ? (size_t)BK : (size_t)BK * g.lda, step_b = B_KC ? (size_t)BK : (size_t)BK * g.ldb;
+    const u16 *const base_a = A_KC ? g.A + (size_t)i0 * g.lda + kbeg : g.A + (size_t)kbeg * g.lda + i0;
+    const u16 *const base_b = B_KC ? g.B + (size_t)j0 * g.ldb + kbeg : g.B + (size_t)kbeg * g.ldb + j0;
+    const int records_a = PA::records(g.lda, g.M - i0), records_b = PB::records(g.ldb, g.N - j0);
+    // The partial step, if there is one, is the first; the full steps follow, and loads beyond the last read as zero, without
+    // traffic.
+    int next = 0;
+    __amdgpu_buffer_rsrc_t rsa, rsb, rsl, rsy;
+    auto point_at = [&](const int full) {
+        const bool more = full < nfull;
+        rsa = __builtin_amdgcn_make_buffer_rsrc((void *)(base_a + step_a * full), 0, more ? records_a : 0, 0x00020000);
+        rsb = __builtin_amdgcn_make_buffer_rsrc((void *)(base_b + step_b * full), 0, more ? records_b : 0, 0x00020000);
+        if constexpr (DELTA_B) {
+            rsl = __builtin_amdgcn_make_buffer_rsrc((void *)(g.row_lse + kbeg + full * BK), 0, more ? BK * 4 : 0, 0x00020000);
+            rsy = __builtin_amdgcn_make_buffer_rsrc((void *)(g.labels + kbeg + full * BK), 0, more ? BK * 4 : 0, 0x00020000);
+        }
+    };
+
+    // DELTA: a vector of logits becomes the output delta on its way to LDS.  The label falls into few vectors: 16 of 100
+    // wavefronts' at 3203 classes have one at all.
+    constexpr float LOG2E = 1.44269504088896340736f;
+    auto to_delta = [&](u16x8 &reg, const float nl, const int lab) {   // nl = -lse*log2(e); lab relative to element 0
+        const uintx4_t raw = __builtin_bit_cast(uintx4_t, reg);
+        float d[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float x = __uint_as_float((e & 1) ? (raw[e >> 1] & 0xffff0000u) : (raw[e >> 1] << 16));
+            d[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(x, LOG2E, nl));
+        }
+        if (__any((unsigned)lab < 8u)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d[e] -= lab == e ? 1.0f : 0.0f;
+        }
+        reg = f32x8_to_bf16x8(d);
+    };
+    float a_nl[DELTA_A ? NA : 1];                  // -lse * log2(e) of a vector's row (fixed for all steps), and its label
+    int a_lab[DELTA_A ? NA : 1];
+    if constexpr (DELTA_A) {
+#pragma unroll
+        for (int v = 0; v < NA; ++v) {
+            const int r = min(PA::row(tid, v), g.M - i0 - 1);
+            a_nl[v] = -g.row_lse[i0 + r] * LOG2E;
+            a_lab[v] = g.labels[i0 + r] - kbeg - PA::col(tid);
+        }
+    }
+    float b_lse[DELTA_B ? NB : 1];                 // of a vector's pattern, fetched with it
+    int b_lab[DELTA_B ? NB : 1];
+    auto fetch_unit = [&](auto j) {
+        constexpr int J = decltype(j)::value;
+        if constexpr (J < NA) {
+            pa.template fetch<J>(rsa, g.lda);
+        } else {
+            pb.template fetch<J - NA>(rsb, g.ldb);
+            if constexpr (DELTA_B) {
+                b_lse[J - NA] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsl, PB::row(tid, J - NA) * 4, 0, 0));
+                b_lab[J - NA] = (int)__builtin_amdgcn_raw_buffer_load_b32(rsy, PB::row(tid, J - NA) * 4, 0, 0);
+            }
+        }
+    };
+    auto fetch_next = [&] {
+        point_at(next++);
+        for_each_index<NU>(fetch_unit);
+    };
+    auto unit = [&](auto j, u16 *stage) {
+        constexpr int J = decltype(j)::value;
+        if constexpr (J < NA) {
+            if constexpr (DELTA_A) {
+                to_delta(pa.reg[J], a_nl[J], a_lab[J]);
+                a_lab[J] -= BK;
+            }
+            pa.template store<J>(stage);
+        } else {
+            if constexpr (DELTA_B) to_delta(pb.reg[J - NA], -b_lse[J - NA] * LOG2E, b_lab[J - NA] - j0 - PB::col(tid));
+            pb.template store<J - NA>(stage + B0);
+        }
+    };
+
+    // Stage 0 takes the first step, the registers the second.
+    if (left) {
+        // (logits of minus infinity: the delta of the classes beyond the range is zero)
+        pa.fetch_partial(base_a + step_a * nfull, g.lda, g.M - i0, left, tid, DELTA_A ? (u16)0xff80 : (u16)0);
+        pb.fetch_partial(base_b + step_b * nfull, g.ldb, g.N - j0, left, tid);
+        if constexpr (DELTA_A) {
+#pragma unroll
+            for (int v = 0; v < NA; ++v) a_lab[v] -= nfull * BK;
+        }
+        if constexpr (DELTA_B) {
+#pragma unroll
+            for (int v = 0; v < NB; ++v) {
+                const int r = PB::row(tid, v);
+                b_lse[v] = r < left ? g.row_lse[kbeg + nfull * BK + r] : INFINITY;
+                b_lab[v] = r < left ? g.labels[kbeg + nfull * BK + r] : -8;
+            }
+        }
+    } else {
+        fetch_next();
+    }
+    for_each_index<NU>([&](auto j) { unit(j, lds); });
+    if constexpr (DELTA_A) {
+        if (left) {
+#pragma unroll
+            for (int v = 0; v < NA; ++v) a_lab[v] += nfull * BK + BK;
+        }
+    }
+    fetch_next();
+    __syncthreads();
+
+    constexpr bool A_LONG = RM > RN;
+    constexpr int NS = A_LONG ? RN : RM, NL = A_LONG ? RM : RN;
+    using PS = std::conditional_t<A_LONG, PB, PA>;
+    using PL = std::conditional_t<A_LONG, PA, PB>;
+    int frag_s[2], frag_l[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        frag_s[t] = A_LONG ? B0 + PB::fragment(wcol, lane, t) : PA::fragment(wrow, lane, t);
+        frag_l[t] = A_LONG ? PA::fragment(wrow, lane, t) : B0 + PB::fragment(wcol, lane, t);
+    }
+    bf16x8 f[2][NS], q[2][2];
+    auto read_f = [&](const u16 *from, const int t) {
+#pragma unroll
+        for (int x = 0; x < NS; ++x) f[t][x] = PS::read(from + frag_s[t], x);
+    };
+    auto read_q = [&](const u16 *from, const int l) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) q[l & 1][t] = PL::read(from + frag_l[t], l);
+    };
+    read_q(lds, 0);
+    read_f(lds, 0);
+    read_f(lds, 1);
+    int s = 0;
+    if (steps > 0)
+#pragma unroll 1
+    do {
+        const u16 *const here = lds + (s & 1) * STAGE;
+        u16 *const other = lds + ((s & 1) ^ 1) * STAGE;
+        point_at(next++);
+        auto multiply = [&](auto block, const int t) {
+            constexpr int B = decltype(block)::value;
+#pragma unroll
+            for (int x = 0; x < NS; ++x) {
+                floatx4 &c = acc[A_LONG ? B : x][A_LONG ? x : B];
+                if constexpr (A_LONG) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t][x], q[B & 1][t], c, 0, 0, 0);
+                else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[B & 1][t], f[t][x], c, 0, 0, 0);
+            }
+        };
+        for_each_index<NL>([&](auto block) {
+            constexpr int B = decltype(block)::value;
+            if constexpr (B + 1 < NL) {
+                read_q(here, B + 1);
+                multiply(block, 0);
+                multiply(block, 1);
+                constexpr int U0 = B * NU / (NL - 1), U1 = (B + 1) * NU / (NL - 1);
+                for_each_index<U1 - U0>([&](auto j) {
+                    unit(std::integral_constant<int, U0 + decltype(j)::value>{}, other);
+                    fetch_unit(std::integral_constant<int, U0 + decltype(j)::value>{});
+                });
+            } else {
+                // Behind the barrier the other stage is whole and nothing reads this one: the last block's products cover
+                // the latency of the next step's first fragments.
+                __syncthreads();
+                read_q(other, 0);
+                multiply(block, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                read_f(other, 0);
+                multiply(block, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                read_f(other, 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    } while (++s < steps);
+    static_assert(2 * STAGE * 2 >= Cfg::WM * Cfg::WN * EPILOGUE_SCRATCH_FLOATS * 4, "epilogue scratch fits in the panels' LDS");
+    gemm16_epilogue<Cfg, EPI>(g, acc, reinterpret_cast<float *>(lds) + wave * EPILOGUE_SCRATCH_FLOATS, i0, j0, z, tile_n);
+}
+
+template <class Cfg, bool A_KC, bool B_KC, int EPI, int DELTA = 0>
+__global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void wide16_kernel(const Gemm16Args g)
+{
+    __shared__ __attribute__((aligned(16))) u16 lds[2 * wide16_stage<Cfg, A_KC, B_KC>()];
+    wide16_tile<Cfg, A_KC, B_KC, EPI, DELTA>(g, blockIdx.y * gridDim.x + blockIdx.x, gridDim.y, lds);
 }
 
 }  // namespace ulsnn

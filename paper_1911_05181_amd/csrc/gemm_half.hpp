@@ -43,9 +43,6 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <type_traits>
-#include <utility>
-
 #include "gemm_split.hpp"
 
 namespace ulsnn {
@@ -129,21 +126,11 @@ __device__ __forceinline__ float wave_max(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-template <class F, int... I>
-__device__ __forceinline__ void call_with(F &&f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
 // The same value, as far as the compiler knows another one: what is derived from it is neither formed early nor kept alive.
 __device__ __forceinline__ int fresh(int x)
 {
     asm volatile("" : "+v"(x));
     return x;
-}
-template <int N, class F>
-__device__ __forceinline__ void for_each_index(F &&f)
-{
-    call_with(f, std::make_integer_sequence<int, N>{});
 }
 
 // One thread's share of a panel of R rows: loads, terms, range check.  It comes in units of W k of one row: 4 (KC) or, with

@@ -295,7 +295,7 @@ hipError_t launch_reduce(int splits, int epi, const GemmArgs &a, const float *pa
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// bf16-operand GEMM dispatch (fp32 accumulation): two tile shapes, same cost model with the measured bf16 rate
+// bf16-operand GEMM dispatch (fp32 accumulation): tile shapes, same cost model with the measured bf16 rate
 // ---------------------------------------------------------------------------------------------------------
 
 using T16_128 = Tile16<128, 128, 2, 2, 4, 1>;   // 256 threads, 4 workgroups / CU (LDS 39 KB each)
@@ -303,10 +303,12 @@ using T16_64 = Tile16<64, 64, 2, 2, 8, 1>;      // 256 threads, 8 workgroups / C
 // Wavefront sub-tile 128 x 64: a third fewer LDS bytes per matrix instruction than 64 x 64 (the 128x128 shape is
 // bound by LDS reads).  Two workgroups per CU, so the epilogue's stores are poorly hidden: long-k products only.
 using T16_256 = Tile16<256, 128, 2, 2, 2, 2>;
-// 256 x 256 with eight wavefronts (sub-tile 64 x 128), one workgroup per CU: a third less operand traffic per
-// product again.  Measured on the hidden-delta product (both operands k-contiguous): 164 -> 140 us at 32768 patterns;
-// on the dW2 product (both m-contiguous) at 65536 patterns: backward products 645 -> 618 us.
-using T16_256x256 = Tile16<256, 256, 4, 2, 2, 2>;
+// 256 x 256 with eight wavefronts, one workgroup per CU: a third less operand traffic per product again, and steps of 64 k
+// (wide16_kernel).  The sub-tile lies across or along by what each read costs: with both operands k-contiguous 64 x 128 and
+// 128 x 64 measured the same on plain products, the hidden delta 237 and 243 us at 65536 patterns; with both m-contiguous
+// (dW2 there) 261 and 249.
+using T16_256x256 = Wide16<256, 256, 4, 2, 2>;
+using T16_256x256t = Wide16<256, 256, 2, 4, 2>;
 
 enum Cfg16Id { CFG16_128 = 0, CFG16_64, CFG16_256, CFG16_256x256, CFG16_COUNT };
 constexpr int CFG16_256_MIN_K = 1024;
@@ -315,7 +317,7 @@ constexpr CfgInfo CFG16_INFO[CFG16_COUNT] = {
     {128, 128, 32, 256, 4, 1.00, "bf16 128x128"},
     {64, 64, 32, 256, 8, 0.70, "bf16 64x64"},
     {256, 128, 32, 256, 2, 1.30, "bf16 256x128"},
-    {256, 256, 32, 512, 1, 1.55, "bf16 256x256"},
+    {256, 256, 64, 512, 1, 1.83, "bf16 256x256"},     // (1.83 x the 2-wavefront utilisation: 4096^3 in 115 us)
 };
 constexpr double BF16_SUSTAINED_FLOPS = 800.0e12;   // what the 128x128 bf16 tile sustains on large problems
 
@@ -326,14 +328,17 @@ struct Gemm16Plan {
     double est_us;
 };
 
-Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_split, size_t max_partial_floats)
+// `wide`: the operands suit wide16_kernel, which loads whole vectors with 32-bit offsets within a panel of 256 rows: 16-byte
+// aligned rows shorter than WIDE16_MAX_LD.
+constexpr int WIDE16_MAX_LD = 1 << 22;
+Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_split, size_t max_partial_floats, bool wide)
 {
     Gemm16Plan best{};
     best.est_us = 1e30;
     for (int ci = 0; ci < CFG16_COUNT; ++ci) {
         const CfgInfo &c = CFG16_INFO[ci];
-        if (ci == CFG16_256 && k < CFG16_256_MIN_K) continue;
-        if (ci == CFG16_256x256 && !(a_kc == b_kc && k >= CFG16_256_MIN_K)) continue;   // NT and TN long-k products
+        if ((ci == CFG16_256 || ci == CFG16_256x256) && k < CFG16_256_MIN_K) continue;
+        if (ci == CFG16_256x256 && !wide) continue;
         int max_splits = allow_split ? std::max(1, std::min(64, k / (8 * c.bk))) : 1;
         if ((size_t)m * n > 0) max_splits = (int)std::min<size_t>(max_splits, std::max<size_t>(1, max_partial_floats / ((size_t)m * n)));
         for (int s = 1; s <= max_splits; ++s) {
@@ -357,7 +362,12 @@ template <class Cfg, bool A_KC, bool B_KC, int EPI, int DELTA = 0>
 hipError_t launch16_one(const Gemm16Args &a, int splits, hipStream_t s)
 {
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)splits);
-    hipLaunchKernelGGL((gemm16_kernel<Cfg, A_KC, B_KC, EPI, DELTA>), grid, dim3(Cfg::THREADS), 0, s, a);
+    if constexpr (std::is_same_v<Cfg, T16_256x256> && !A_KC && !B_KC)
+        hipLaunchKernelGGL((wide16_kernel<T16_256x256t, A_KC, B_KC, EPI, DELTA>), grid, dim3(Cfg::THREADS), 0, s, a);
+    else if constexpr (std::is_same_v<Cfg, T16_256x256>)
+        hipLaunchKernelGGL((wide16_kernel<Cfg, A_KC, B_KC, EPI, DELTA>), grid, dim3(Cfg::THREADS), 0, s, a);
+    else
+        hipLaunchKernelGGL((gemm16_kernel<Cfg, A_KC, B_KC, EPI, DELTA>), grid, dim3(Cfg::THREADS), 0, s, a);
     return hipGetLastError();
 }
 
@@ -418,6 +428,7 @@ hipError_t launch_gemm16(const Gemm16Plan &p, bool a_kc, bool b_kc, int epi, Gem
         if (epi == EPI_AXPBY && !a_kc && !b_kc) return launch16_one<Cfg, false, false, EPI_AXPBY>(a, p.splits, s);
         return hipErrorInvalidValue;
     };
+    if (p.cfg == CFG16_256x256 && (!a.aligned || (c_bf16 && !a.c_vec))) return hipErrorInvalidValue;   // (plan_gemm16's `wide`)
     return p.cfg == CFG16_128 ? go(T16_128{}) : p.cfg == CFG16_256 ? go(T16_256{})
          : p.cfg == CFG16_256x256 ? go(T16_256x256{}) : go(T16_64{});
 }
@@ -862,11 +873,13 @@ int mlp_grad_impl16(const ulsnn_mlp_desc *d, const u16 *W1, const u16 *W2, const
         const bool copy_x = !rows_16b_aligned(Xs, n_in) && (task.backward ? rows >= 128 : n_in > 64) &&
                             (size_t)rows * ldx_copy * sizeof(u16) <= half_pb * sizeof(float);
         const size_t floats_pb = copy_x ? half_pb : L.floats_pb;
-        const Gemm16Plan p1 = plan_gemm16(rows, n_hid, n_in, true, false, false, 0);
-        const Gemm16Plan p2 = plan_gemm16(rows, n_out, n_hid, true, false, false, 0);
-        const Gemm16Plan p3 = plan_gemm16(n_hid, n_out, rows, false, false, true, L.floats_pa);
-        const Gemm16Plan p4 = plan_gemm16(rows, n_hid, n_out, true, true, true, floats_pb);
-        const Gemm16Plan p5 = plan_gemm16(n_in, n_hid, rows, false, false, true, floats_pb);
+        // (the copies of the weights and everything in the workspace are aligned)
+        const bool wide = std::max(std::max(n_in, n_hid), n_out) <= WIDE16_MAX_LD - 32, wide_x = wide && (copy_x || rows_16b_aligned(Xs, n_in));
+        const Gemm16Plan p1 = plan_gemm16(rows, n_hid, n_in, true, false, false, 0, wide_x);
+        const Gemm16Plan p2 = plan_gemm16(rows, n_out, n_hid, true, false, false, 0, wide);
+        const Gemm16Plan p3 = plan_gemm16(n_hid, n_out, rows, false, false, true, L.floats_pa, wide);
+        const Gemm16Plan p4 = plan_gemm16(rows, n_hid, n_out, true, true, true, floats_pb, wide);
+        const Gemm16Plan p5 = plan_gemm16(n_in, n_hid, rows, false, false, true, floats_pb, wide_x);
         Gemm16Args a{};
         MARK(0);
 

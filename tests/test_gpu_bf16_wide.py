@@ -1,0 +1,75 @@
+"""The 256 x 256 tile of the bf16 products (wide16_kernel) where it can go wrong: a partial k step in every product, ragged
+last tiles, k slices, logits far from zero, labels outside the classes, patterns whose rows are not 16-byte aligned.
+
+Bar: relative L2 1e-2 per tensor, as for every bf16 gradient: H, the output delta and the hidden delta are rounded to bf16
+(2^-9 relative each, so about 3.4e-3 where the three do not average out); three of 3203 classes lost would be 3e-2.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1911_05181_amd as ulsnn
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TOL = 1e-2
+
+
+def _rel(a, b):
+    return np.linalg.norm(a.cpu().numpy().astype(np.float64) - b) / np.linalg.norm(b)
+
+
+def _np(t):
+    return None if t is None else t.float().numpy()
+
+
+def _dev(t):
+    return None if t is None else t.to(DEV)
+
+
+@pytest.mark.parametrize("n_in,n_hid,n_out,batch,dense", [
+    (1030, 1100, 1500, 9000, False),    # all five products on the tile; k = 1030, 1100, 1500, 9000: all with a remainder
+    (1030, 1100, 1500, 4097, True),
+    (1088, 1088, 1536, 8192, False),    # no remainder anywhere
+    (300, 1300, 2051, 8191, False),     # both backward products of the output layer, remainders 3 and 63
+    (400, 480, 3203, 16384, False),     # hidden delta in k slices
+])
+def test_gradient(n_in, n_hid, n_out, batch, dense):
+    shape = si.MlpShape(n_in, n_hid, n_out, True)
+    W1, W2, _, _ = si.mlp_weights(shape, 3)
+    b1, b2 = si.random_biases(shape, 3, 0.2)
+    X, y = si.mlp_patterns(shape, 3, 0, batch)
+    W1, W2, X = W1.bfloat16(), W2.bfloat16(), X.bfloat16()
+    weights = (_dev(W1), _dev(W2), _dev(X))
+    if dense:
+        t = torch.tanh(torch.randn(batch, n_out, generator=torch.Generator().manual_seed(3)))
+        ref = oracle.mlp_grad_mse(_np(W1), _np(W2), _np(X), _np(t), _np(b1), _np(b2))
+        call = lambda: ulsnn.mlp_grad_mse(*weights, _dev(t), _dev(b1), _dev(b2))
+    else:
+        y[[0, 5, batch - 1]] = torch.tensor([-1, n_out, 2 ** 30], dtype=y.dtype)      # no class: no gradient
+        y[1:5] = torch.tensor([0, n_out - 1, 63, 64], dtype=y.dtype)
+        ref = oracle.mlp_grad(_np(W1), _np(W2), _np(X), y.numpy(), _np(b1), _np(b2))
+        call = lambda: ulsnn.mlp_grad(*weights, _dev(y), _dev(b1), _dev(b2))
+    res, again = call(), call()
+    torch.cuda.synchronize()
+    errors = {name: _rel(getattr(res, name), getattr(ref, name)) for name in ("dW1", "dW2", "db1", "db2")}
+    errors["loss"] = abs(res.loss.item() - ref.loss) / abs(ref.loss)
+    print(n_in, n_hid, n_out, batch, {k: f"{e:.1e}" for k, e in errors.items()})
+    assert max(errors.values()) <= TOL, errors
+    for name in ("dW1", "dW2", "db1", "db2", "loss"):
+        assert torch.equal(getattr(res, name), getattr(again, name)), name
+
+
+def test_far_logits_and_a_partial_step():
+    """All logits -128 (exact in bf16): exp(-log sum exp) overflows, so classes beyond the last must not form a delta."""
+    shape = si.MlpShape(300, 1300, 2051, True)
+    W1, W2, b1, _ = si.mlp_weights(shape, 3)
+    X, y = si.mlp_patterns(shape, 3, 0, 8191)
+    W1, W2, X, b2 = W1.bfloat16(), torch.zeros_like(W2).bfloat16(), X.bfloat16(), torch.full((2051,), -128.0)
+    ref = oracle.mlp_grad(_np(W1), _np(W2), _np(X), y.numpy(), _np(b1), _np(b2))
+    res = ulsnn.mlp_grad(_dev(W1), _dev(W2), _dev(X), _dev(y), _dev(b1), _dev(b2))
+    torch.cuda.synchronize()
+    assert not res.dW1.any() and not res.db1.any()
+    assert _rel(res.dW2, ref.dW2) <= TOL and _rel(res.db2, ref.db2) <= TOL
