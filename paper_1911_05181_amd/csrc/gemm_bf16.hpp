@@ -85,13 +85,9 @@ struct Gemm16Args {
     int aux_vec;           // 1: rows of aux are 16-byte aligned
 };
 
-// PREFETCH_ = k steps kept in flight in registers.  A bf16 step is eight times shorter on the matrix cores than an
-// fp32 one, so a single step of products does not cover the latency of the next step's global loads.
-template <int BM_, int BN_, int WM_, int WN_, int WAVES_PER_SIMD_ = 1, int PREFETCH_ = 1>
+template <int BM_, int BN_, int WM_, int WN_, int WAVES_PER_SIMD_ = 1>
 struct Tile16 {
     static constexpr int BM = BM_, BN = BN_, BK = 32, WM = WM_, WN = WN_, WAVES_PER_SIMD = WAVES_PER_SIMD_;
-    static constexpr int PREFETCH = PREFETCH_;
-    static_assert(PREFETCH_ >= 1, "prefetch depth");
     static constexpr int THREADS = WM * WN * 64;
     static constexpr int WTM = BM / WM, WTN = BN / WN;
     static constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -610,18 +606,12 @@ __device__ __forceinline__ void gemm16_tile(const Gemm16Args &g, const int hw, c
     const size_t step_a = A_KC ? (size_t)BK : (size_t)BK * g.lda;
     const size_t step_b = B_KC ? (size_t)BK : (size_t)BK * g.ldb;
 
-    constexpr int D = Cfg::PREFETCH;
-    // Register slots of the fetch pipeline: while step kb is multiplied out of LDS, the loads of steps
-    // kb+1 .. kb+D are in flight; step s lives in slot s % D (the loops below are unrolled so that slot numbers are
-    // compile-time constants).
-    u16x8 ra[D][NVA], rb[D][NVB];
+    // While step kb is multiplied out of LDS, the loads of step kb + 1 are in flight.
+    u16x8 ra[NVA], rb[NVB];
 #pragma unroll
-    for (int u = 0; u < D; ++u) {
+    for (int v = 0; v < NVA; ++v) ra[v] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int v = 0; v < NVA; ++v) ra[u][v] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int v = 0; v < NVB; ++v) rb[u][v] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    }
+    for (int v = 0; v < NVB; ++v) rb[v] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
 
     // DELTA: the logits in the fetch registers become the output delta just before they are stored to LDS (the
     // transform is issued ahead of the matrix instructions of the step that hides it).
@@ -669,34 +659,34 @@ __device__ __forceinline__ void gemm16_tile(const Gemm16Args &g, const int hw, c
     };
     // DELTA 2 (B, m-contiguous): a vector is eight classes of ONE pattern, and the pattern (the k row) changes with
     // every step, so log-sum-exp and label of a vector's pattern travel with the panel: they are loaded when the
-    // panel is fetched, into the same register slot.  A k row beyond the range (partial last step, zero filled)
+    // panel is fetched.  A k row beyond the range (partial last step, zero filled)
     // gets -inf, which keeps it zero.
     static_assert(!DELTA_B || (BN * BK / 8) % THREADS == 0, "every thread owns whole vectors of the B panel");
     // (The loaded values are kept raw until the panel is stored: arithmetic on them at fetch time would make the
     // compiler wait for the loads on the spot.)
-    float b_lse[Cfg::PREFETCH][NVB];
-    int b_lab[Cfg::PREFETCH][NVB];
-    auto fetch_b_meta = [&](const int slot, const int k_first, const bool checked) {
+    float b_lse[NVB];
+    int b_lab[NVB];
+    auto fetch_b_meta = [&](const int k_first, const bool checked) {
         if constexpr (DELTA_B) {
 #pragma unroll
             for (int v = 0; v < NVB; ++v) {
                 const int k = k_first + (tid + v * THREADS) / (BN / 8);
                 if (!checked || k < kend) {
-                    b_lse[slot][v] = g.row_lse[k];
-                    b_lab[slot][v] = g.labels[k];
+                    b_lse[v] = g.row_lse[k];
+                    b_lab[v] = g.labels[k];
                 } else {
-                    b_lse[slot][v] = INFINITY;
-                    b_lab[slot][v] = -8;
+                    b_lse[v] = INFINITY;
+                    b_lab[v] = -8;
                 }
             }
         }
     };
-    auto prepare_b = [&](const int slot, u16x8 (&reg)[NVB]) {
+    auto prepare_b = [&](u16x8 (&reg)[NVB]) {
         if constexpr (DELTA_B) {
 #pragma unroll
             for (int v = 0; v < NVB; ++v) {
                 const int col0 = j0 + ((tid + v * THREADS) % (BN / 8)) * 8;     // class of the vector's first element
-                to_delta(reg[v], -b_lse[slot][v] * LOG2E, b_lab[slot][v] - col0);
+                to_delta(reg[v], -b_lse[v] * LOG2E, b_lab[v] - col0);
             }
         }
     };
@@ -706,31 +696,26 @@ __device__ __forceinline__ void gemm16_tile(const Gemm16Args &g, const int hw, c
 
     const u16 *na = pa, *nb = pb;   // where the next unchecked fetch reads ...
     int nk = kbeg;                  // ... and the k it starts at
-    auto fetch_full = [&](const int slot) {
-        fa.fetch(ra[slot], na, tid);
-        fb.fetch(rb[slot], nb, tid);
-        fetch_b_meta(slot, nk, false);
+    auto fetch_full = [&] {
+        fa.fetch(ra, na, tid);
+        fb.fetch(rb, nb, tid);
+        fetch_b_meta(nk, false);
         na += step_a;
         nb += step_b;
         nk += BK;
     };
-    auto fetch_checked = [&](const int slot, const int k0) {
-        panel16_fetch_checked<A_KC, BM, THREADS, NVA, A_KC && !B_KC>(ra[slot], g.A, g.lda, i0, g.M, k0, kend, tid, g.aligned != 0);
-        panel16_fetch_checked<B_KC, BN, THREADS, NVB, A_KC && !B_KC>(rb[slot], g.B, g.ldb, j0, g.N, k0, kend, tid, g.aligned != 0);
-        fetch_b_meta(slot, k0, true);
+    auto fetch_checked = [&](const int k0) {
+        panel16_fetch_checked<A_KC, BM, THREADS, NVA, A_KC && !B_KC>(ra, g.A, g.lda, i0, g.M, k0, kend, tid, g.aligned != 0);
+        panel16_fetch_checked<B_KC, BN, THREADS, NVB, A_KC && !B_KC>(rb, g.B, g.ldb, j0, g.N, k0, kend, tid, g.aligned != 0);
+        fetch_b_meta(k0, true);
     };
     if (nkb > 0) {
-        if (nfull > 0) {
-#pragma unroll
-            for (int u = 0; u < D; ++u)
-                if (u < nfull) fetch_full(u);
-        } else {
-            fetch_checked(0, kbeg);
-        }
-        prepare_a(ra[0], kbeg, nfull == 0);
-        prepare_b(0, rb[0]);
-        store_a(stage_a(0), ra[0]);
-        panel16_store<B_KC, BN, THREADS, NVB>(stage_b(0), rb[0], tid);
+        if (nfull > 0) fetch_full();
+        else fetch_checked(kbeg);
+        prepare_a(ra, kbeg, nfull == 0);
+        prepare_b(rb);
+        store_a(stage_a(0), ra);
+        panel16_store<B_KC, BN, THREADS, NVB>(stage_b(0), rb, tid);
     }
     __syncthreads();
 
@@ -751,63 +736,21 @@ __device__ __forceinline__ void gemm16_tile(const Gemm16Args &g, const int hw, c
         }
     };
 
-    // Full steps 0 .. nfull-1.  On entry to step kb its panels are in LDS stage kb & 1 and slot kb % D is free.
-    // Steady state first: while every step of a round of D still has a step D ahead to fetch, the round is
-    // branch-free, so the compiler's wait for the slot being stored leaves the newer loads in flight (at a join
-    // of "fetched" and "not fetched" paths it would have to wait for everything, which defeats the pipeline).
-    int base = 0;
-    if constexpr (D > 1) {
-    for (; base + 2 * D <= nfull; base += D) {
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            const int cur = (base + u) & 1;
-            const int un = (u + 1) % D;
-            fetch_full(u);
-            prepare_a(ra[un], kbeg + (base + u + 1) * BK, false);   // independent of the products below
-            prepare_b(un, rb[un]);
-            compute(cur);
-            store_a(stage_a(cur ^ 1), ra[un]);
-            panel16_store<B_KC, BN, THREADS, NVB>(stage_b(cur ^ 1), rb[un], tid);
-            if constexpr (DELTA_B) {
-                // The dW2 product has the least idle time of all: left to itself the compiler puts the transform in
-                // one block ahead of the matrix instructions, and with every wavefront of the workgroup in step
-                // (a barrier per k step) the two kinds of work then take turns instead of overlapping.  Ask for one
-                // matrix instruction followed by the vector instructions that fit in its shadow (5 plain + 1
-                // transcendental; 3, 4 and 6 measured slower, and on the hidden-delta product any such order was).
-#pragma unroll
-                for (int i = 0; i < 2 * TM * TN; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 matrix instruction
-                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);   // 5 vector ALU instructions
-                    __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);   // 1 transcendental
-                }
-            }
-            __syncthreads();
+    // Full steps 0 .. nfull-1.  On entry to step kb its panels are in LDS stage kb & 1.
+    for (int kb = 0; kb < nfull; ++kb) {
+        const int cur = kb & 1, next = kb + 1;
+        if (next < nfull) fetch_full();
+        if (next == nfull && next < nkb) fetch_checked(kbeg + next * BK);      // the partial last step: zero filled
+        if (next < nkb) {
+            prepare_a(ra, kbeg + next * BK, next == nfull);
+            prepare_b(rb);
         }
-    }
-    }
-    // Drain: the last rounds, where fetches run out (with a single slot: every step).
-    for (; base < nfull; base += D) {
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            const int kb = base + u;
-            if (kb < nfull) {
-                const int cur = kb & 1, next = kb + 1;
-                const int un = (u + 1) % D;            // slot of step kb + 1
-                if (kb + D < nfull) fetch_full(u);     // refill the free slot with step kb + D
-                if (next == nfull && next < nkb)       // the partial last step: checked fetch, zero filled
-                    fetch_checked(un, kbeg + next * BK);
-                if (next < nkb) {
-                    prepare_a(ra[un], kbeg + next * BK, next == nfull);
-                    prepare_b(un, rb[un]);
-                }
-                compute(cur);
-                if (next < nkb) {
-                    store_a(stage_a(cur ^ 1), ra[un]);
-                    panel16_store<B_KC, BN, THREADS, NVB>(stage_b(cur ^ 1), rb[un], tid);
-                }
-                __syncthreads();
-            }
+        compute(cur);
+        if (next < nkb) {
+            store_a(stage_a(cur ^ 1), ra);
+            panel16_store<B_KC, BN, THREADS, NVB>(stage_b(cur ^ 1), rb, tid);
         }
+        __syncthreads();
     }
     // Steps from nfull on: the one partial step after full ones (already in LDS), or every step of an operand
     // without 16-byte aligned rows (nfull == 0).
@@ -815,14 +758,14 @@ __device__ __forceinline__ void gemm16_tile(const Gemm16Args &g, const int hw, c
         const int cur = kb & 1;
         const bool more = kb + 1 < nkb;
         if (more) {
-            fetch_checked(0, kbeg + (kb + 1) * BK);
-            prepare_a(ra[0], kbeg + (kb + 1) * BK, true);
-            prepare_b(0, rb[0]);
+            fetch_checked(kbeg + (kb + 1) * BK);
+            prepare_a(ra, kbeg + (kb + 1) * BK, true);
+            prepare_b(rb);
         }
         compute(cur);
         if (more) {
-            store_a(stage_a(cur ^ 1), ra[0]);
-            panel16_store<B_KC, BN, THREADS, NVB>(stage_b(cur ^ 1), rb[0], tid);
+            store_a(stage_a(cur ^ 1), ra);
+            panel16_store<B_KC, BN, THREADS, NVB>(stage_b(cur ^ 1), rb, tid);
         }
         __syncthreads();
     }
@@ -839,9 +782,10 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void gemm16_kern
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// The large tile of the long products: 256 x 256 by eight wavefronts, one workgroup per CU, steps of 64 k.
+// The tiles with steps of 64 k: 256 x 256 by eight wavefronts, one workgroup per CU, for the longest products, and 128 x 128 by
+// eight, two workgroups, for those that leave compute units idle or end in a long epilogue otherwise.
 //
-// Per step a wavefront issues 64 instructions of 16 x 16 x 32 (the 32 x 32 x 16 form reaches a tenth less: power), 0.95 us of
+// Per step of 256 x 256 a wavefront issues 64 instructions of 16 x 16 x 32 (the 32 x 32 x 16 form reaches a tenth less: power), 0.95 us of
 // matrix time per step; the fragments' LDS reads take 0.7 us and the panels' writes 0.25 us beside them, so what the step costs
 // beyond that is latency, and the loop is laid out to hide it:
 //   * one set of staging registers: a vector goes to the other LDS stage between the products of two fragments and the same
@@ -852,9 +796,11 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void gemm16_kern
 //     (loads beyond the last step go to an empty buffer and read as zero).
 // Against the tile it took the place of (32 k per step, two register sets, 32 x 32 x 16): 4096^3 NT 136 -> 115 us (1.20 PFLOP/s),
 // TN 134 -> 118; at 65536 patterns of 400-480-3203 (1.7 % of k is padding, 6 % of the rows) the hidden delta 282 -> 237 us,
-// without forming the delta 255 -> 214; dW2 286 -> 249, without 245 -> 203; dW1 44 -> 39.  The gradient: 1019 -> 930 us, of
-// 1024-1024-4096 at 20000 patterns 834 -> 700.  At k = 480 (output layer) it gives 362 against 372 us for the 128 x 128 tile at
+// without forming the delta 255 -> 214; dW2 286 -> 249, without 245 -> 203; dW1 44 -> 39.  The gradient: 1019 -> 930 us.  At k = 480 (output layer) it gives 362 against 372 us for the 128 x 128 tile at
 // 65536 patterns and loses at 10000 (87 against 80): its stores wait for nothing to overlap with, so short k keeps that one.
+// 128 x 128 against the tiles with steps of 32 k (128 x 128, 64 x 64), best number of slices each, 400-480-3203: hidden delta at
+// 1024 patterns 11.4 us (18), 4096 25.4 (33), dW2 at 2048 21.3 (24.3), 4096 31.2 (36.7), dW1 at 16384 16.2 (19.1), output layer at
+// 2048 18.7 (20.7).  Gradients: 2048 patterns 163 -> 92 us, 4096 177 -> 126, 8192 222 -> 181.
 // ---------------------------------------------------------------------------------------------------------
 
 template <int BM_, int BN_, int WM_, int WN_, int WAVES_PER_SIMD_>

@@ -92,7 +92,7 @@ inline double simd_utilisation(double w)
 // Estimated run time of one launch (+ the split-k reduction), in microseconds.  Not a simulator: a consistent
 // way to trade tile efficiency against how evenly the workgroups fill 256 compute units.
 double model_us(const CfgInfo &c, bool a_kc, bool b_kc, int m, int n, int k, int splits, int *kchunk_out,
-                int *splits_out, double peak_flops = 155.0e12)
+                int *splits_out)
 {
     const int chunk = (int)round_up((size_t)(k + splits - 1) / splits, c.bk);
     const int sp = (k + chunk - 1) / chunk;
@@ -101,7 +101,7 @@ double model_us(const CfgInfo &c, bool a_kc, bool b_kc, int m, int n, int k, int
     const long tiles = (long)((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
     const long wgs = tiles * sp;
     const double layout = (!a_kc && !b_kc) ? 0.92 : (a_kc && b_kc) ? 1.0 : 0.97;   // 4-byte LDS reads cost more
-    const double cu_rate = peak_flops / 256.0 * c.eff * layout;   // flop/s of one compute unit (peak is for 256 of them)
+    const double cu_rate = 155.0e12 / 256.0 * c.eff * layout;   // flop/s of one compute unit (peak is for 256 of them)
     const double flops_wg = 2.0 * c.bm * c.bn * (double)chunk;
     const double wps = c.threads / 256.0;                                          // wavefronts per SIMD per WG
     const long slots = (long)num_cu() * c.occ;
@@ -295,31 +295,42 @@ hipError_t launch_reduce(int splits, int epi, const GemmArgs &a, const float *pa
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// bf16-operand GEMM dispatch (fp32 accumulation): tile shapes, same cost model with the measured bf16 rate
+// bf16-operand GEMM dispatch (fp32 accumulation): tile shapes and their costs
 // ---------------------------------------------------------------------------------------------------------
 
-using T16_128 = Tile16<128, 128, 2, 2, 4, 1>;   // 256 threads, 4 workgroups / CU (LDS 39 KB each)
-using T16_64 = Tile16<64, 64, 2, 2, 8, 1>;      // 256 threads, 8 workgroups / CU
-// Wavefront sub-tile 128 x 64: a third fewer LDS bytes per matrix instruction than 64 x 64 (the 128x128 shape is
-// bound by LDS reads).  Two workgroups per CU, so the epilogue's stores are poorly hidden: long-k products only.
-using T16_256 = Tile16<256, 128, 2, 2, 2, 2>;
-// 256 x 256 with eight wavefronts, one workgroup per CU: a third less operand traffic per product again, and steps of 64 k
-// (wide16_kernel).  The sub-tile lies across or along by what each read costs: with both operands k-contiguous 64 x 128 and
-// 128 x 64 measured the same on plain products, the hidden delta 237 and 243 us at 65536 patterns; with both m-contiguous
-// (dW2 there) 261 and 249.
+using T16_128 = Tile16<128, 128, 2, 2, 4>;   // 256 threads, 4 workgroups / CU (LDS 39 KB each)
+using T16_64 = Tile16<64, 64, 2, 2, 8>;      // 256 threads, 8 workgroups / CU
+// Steps of 64 k (wide16_kernel): 256 x 256, one workgroup per CU, and 128 x 128, two, both with eight wavefronts.  The sub-tile
+// of the large one lies across or along by what each read costs: with both operands k-contiguous 64 x 128 and 128 x 64 measured
+// the same on plain products, the hidden delta 237 and 243 us at 65536 patterns; with both m-contiguous (dW2 there) 261 and 249.
 using T16_256x256 = Wide16<256, 256, 4, 2, 2>;
 using T16_256x256t = Wide16<256, 256, 2, 4, 2>;
+using T16_128k64 = Wide16<128, 128, 4, 2, 4>;
 
-enum Cfg16Id { CFG16_128 = 0, CFG16_64, CFG16_256, CFG16_256x256, CFG16_COUNT };
-constexpr int CFG16_256_MIN_K = 1024;
+enum Cfg16Id { CFG16_128 = 0, CFG16_64, CFG16_256x256, CFG16_128K64, CFG16_COUNT };
 
-constexpr CfgInfo CFG16_INFO[CFG16_COUNT] = {
-    {128, 128, 32, 256, 4, 1.00, "bf16 128x128"},
-    {64, 64, 32, 256, 8, 0.70, "bf16 64x64"},
-    {256, 128, 32, 256, 2, 1.30, "bf16 256x128"},
-    {256, 256, 64, 512, 1, 1.83, "bf16 256x256"},     // (1.83 x the 2-wavefront utilisation: 4096^3 in 115 us)
+// One launch on an otherwise idle chip, in microseconds, by the layout of its operands (0 a k-contiguous A and an m-contiguous B,
+// 1 both k-contiguous, 2 both m-contiguous): `base`, `more` per further round of workgroups, and per k of the longest slice
+// `slope_1` while every compute unit has at most one workgroup (`idle` of it when hardly any has one), else `slope_r` per round,
+// of which the last counts as whole to the part `full`.  `delta`: what forming the output delta multiplies the slopes by (1.0
+// where the layout never does).  Fitted to 4300 launches of the gradients' five products over 70 networks and batches (48 to
+// 1024 inputs, 32 to 1024 hidden, 10 to 4096 classes, 256 to 40000 patterns), each tile off by 4 (first layout) to 10 percent.
+// The tile and slices it picks take longer than the best of those measured by 0.7 percent (output and hidden layer), 1.9 (hidden
+// delta), 2.3 (dW2) and 1.2 (dW1); one matrix rate for all layouts, which stood here, by 2, 15, 11 and 5.
+struct Tile16Cost {
+    double base, more, slope_1, slope_r, idle, full, delta;
 };
-constexpr double BF16_SUSTAINED_FLOPS = 800.0e12;   // what the 128x128 bf16 tile sustains on large problems
+struct Cfg16Info {
+    int bm, bn, bk;
+    Tile16Cost cost[3];
+    const char *name;
+};
+constexpr Cfg16Info CFG16_INFO[CFG16_COUNT] = {
+    {128, 128, 32, {{8.6, 1.7, 0.0129, 0.0087, 0.91, 1.00, 1.00}, {7.4, 1.2, 0.0183, 0.0098, 0.76, 1.00, 1.22}, {4.9, 0.1, 0.0156, 0.0090, 0.80, 1.00, 1.75}}, "bf16 128x128"},
+    {64, 64, 32, {{5.3, 0.5, 0.0057, 0.0036, 0.91, 0.97, 1.00}, {5.1, 0.4, 0.0089, 0.0043, 0.83, 1.00, 1.24}, {4.0, 0.0, 0.0074, 0.0040, 0.89, 1.00, 2.05}}, "bf16 64x64"},
+    {256, 256, 64, {{16.0, 14.0, 0.0278, 0.0235, 0.53, 0.47, 1.00}, {9.5, 7.1, 0.0248, 0.0242, 0.72, 0.73, 1.19}, {8.2, 10.0, 0.0240, 0.0228, 0.74, 0.66, 1.45}}, "bf16 256x256"},
+    {128, 128, 64, {{6.4, 2.6, 0.0095, 0.0075, 0.73, 1.00, 1.00}, {5.5, 1.5, 0.0096, 0.0080, 0.75, 0.86, 1.33}, {4.6, 2.4, 0.0104, 0.0079, 0.76, 1.00, 1.47}}, "bf16 128x128k64"},
+};
 
 struct Gemm16Plan {
     Cfg16Id cfg;
@@ -329,27 +340,32 @@ struct Gemm16Plan {
 };
 
 // `wide`: the operands suit wide16_kernel, which loads whole vectors with 32-bit offsets within a panel of 256 rows: 16-byte
-// aligned rows shorter than WIDE16_MAX_LD.
+// aligned rows shorter than WIDE16_MAX_LD.  `delta`: the product forms the output delta while loading.
 constexpr int WIDE16_MAX_LD = 1 << 22;
-Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_split, size_t max_partial_floats, bool wide)
+Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_split, size_t max_partial_floats, bool wide, bool delta = false)
 {
     Gemm16Plan best{};
     best.est_us = 1e30;
+    int max_splits = allow_split ? std::max(1, std::min(64, k / 256)) : 1;
+    if ((size_t)m * n > 0) max_splits = (int)std::min<size_t>(max_splits, std::max<size_t>(1, max_partial_floats / ((size_t)m * n)));
     for (int ci = 0; ci < CFG16_COUNT; ++ci) {
-        const CfgInfo &c = CFG16_INFO[ci];
-        if ((ci == CFG16_256 || ci == CFG16_256x256) && k < CFG16_256_MIN_K) continue;
-        if (ci == CFG16_256x256 && !wide) continue;
-        int max_splits = allow_split ? std::max(1, std::min(64, k / (8 * c.bk))) : 1;
-        if ((size_t)m * n > 0) max_splits = (int)std::min<size_t>(max_splits, std::max<size_t>(1, max_partial_floats / ((size_t)m * n)));
+        const Cfg16Info &c = CFG16_INFO[ci];
+        if (c.bk == 64 && !wide) continue;
+        const Tile16Cost &t = c.cost[a_kc && b_kc ? 1 : a_kc ? 0 : 2];
+        const int tiles_m = (m + c.bm - 1) / c.bm, tiles_n = (n + c.bn - 1) / c.bn;
         for (int s = 1; s <= max_splits; ++s) {
-            int chunk, sp;
-            const double us = model_us(c, a_kc, b_kc, m, n, std::max(k, 1), s, &chunk, &sp, BF16_SUSTAINED_FLOPS);
-            if (sp != s) continue;
+            const int chunk = (int)round_up((size_t)(std::max(k, 1) + s - 1) / s, c.bk);
+            if ((std::max(k, 1) + chunk - 1) / chunk != s) continue;      // (fewer slices, seen already)
+            const double r = (double)tiles_m * tiles_n * s / num_cu(), whole = std::ceil(r), slope = delta ? t.delta : 1.0;
+            double us = t.base + (whole - 1.0) * t.more;
+            us += chunk * slope * (r <= 1.0 ? t.slope_1 * (t.idle + (1.0 - t.idle) * r) : t.slope_r * (t.full * whole + (1.0 - t.full) * r));
+            us += (double)m * n * s * (s > 1 || !a_kc ? 4.0 : 2.0) / 8.0e6;      // its stores, beyond what `base` has
+            if (s > 1) us += 3.0 + (double)m * n * (s + 1.0) * 4.0 / 5.0e6;       // the reduction
             if (us < best.est_us) {
                 best.cfg = (Cfg16Id)ci;
-                best.tiles_m = (m + c.bm - 1) / c.bm;
-                best.tiles_n = (n + c.bn - 1) / c.bn;
-                best.splits = sp;
+                best.tiles_m = tiles_m;
+                best.tiles_n = tiles_n;
+                best.splits = s;
                 best.kchunk = chunk;
                 best.est_us = us;
             }
@@ -364,7 +380,7 @@ hipError_t launch16_one(const Gemm16Args &a, int splits, hipStream_t s)
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)splits);
     if constexpr (std::is_same_v<Cfg, T16_256x256> && !A_KC && !B_KC)
         hipLaunchKernelGGL((wide16_kernel<T16_256x256t, A_KC, B_KC, EPI, DELTA>), grid, dim3(Cfg::THREADS), 0, s, a);
-    else if constexpr (std::is_same_v<Cfg, T16_256x256>)
+    else if constexpr (Cfg::BK == 64)
         hipLaunchKernelGGL((wide16_kernel<Cfg, A_KC, B_KC, EPI, DELTA>), grid, dim3(Cfg::THREADS), 0, s, a);
     else
         hipLaunchKernelGGL((gemm16_kernel<Cfg, A_KC, B_KC, EPI, DELTA>), grid, dim3(Cfg::THREADS), 0, s, a);
@@ -378,8 +394,8 @@ inline int stat_group_width(Cfg16Id id)
 {
     switch (id) {
         case CFG16_128: return T16_128::WTN;
-        case CFG16_256: return T16_256::WTN;
         case CFG16_256x256: return T16_256x256::WTN;
+        case CFG16_128K64: return T16_128k64::WTN;
         default: return T16_64::WTN;
     }
 }
@@ -428,9 +444,9 @@ hipError_t launch_gemm16(const Gemm16Plan &p, bool a_kc, bool b_kc, int epi, Gem
         if (epi == EPI_AXPBY && !a_kc && !b_kc) return launch16_one<Cfg, false, false, EPI_AXPBY>(a, p.splits, s);
         return hipErrorInvalidValue;
     };
-    if (p.cfg == CFG16_256x256 && (!a.aligned || (c_bf16 && !a.c_vec))) return hipErrorInvalidValue;   // (plan_gemm16's `wide`)
-    return p.cfg == CFG16_128 ? go(T16_128{}) : p.cfg == CFG16_256 ? go(T16_256{})
-         : p.cfg == CFG16_256x256 ? go(T16_256x256{}) : go(T16_64{});
+    if (CFG16_INFO[p.cfg].bk == 64 && (!a.aligned || (c_bf16 && !a.c_vec))) return hipErrorInvalidValue;   // (plan_gemm16's `wide`)
+    return p.cfg == CFG16_128 ? go(T16_128{}) : p.cfg == CFG16_256x256 ? go(T16_256x256{})
+         : p.cfg == CFG16_128K64 ? go(T16_128k64{}) : go(T16_64{});
 }
 
 // Plan of an unsplit ulsnn_sgemm.
@@ -873,13 +889,14 @@ int mlp_grad_impl16(const ulsnn_mlp_desc *d, const u16 *W1, const u16 *W2, const
         const bool copy_x = !rows_16b_aligned(Xs, n_in) && (task.backward ? rows >= 128 : n_in > 64) &&
                             (size_t)rows * ldx_copy * sizeof(u16) <= half_pb * sizeof(float);
         const size_t floats_pb = copy_x ? half_pb : L.floats_pb;
-        // (the copies of the weights and everything in the workspace are aligned)
-        const bool wide = std::max(std::max(n_in, n_hid), n_out) <= WIDE16_MAX_LD - 32, wide_x = wide && (copy_x || rows_16b_aligned(Xs, n_in));
-        const Gemm16Plan p1 = plan_gemm16(rows, n_hid, n_in, true, false, false, 0, wide_x);
+        // (The copies of the weights and everything in the workspace are aligned.  The hidden layer goes by the patterns as they
+        // came, so that an error with and without gradient has the same sums whether or not they are copied.)
+        const bool wide = std::max(std::max(n_in, n_hid), n_out) <= WIDE16_MAX_LD - 32, x_aligned = rows_16b_aligned(Xs, n_in), softmax = !ts;
+        const Gemm16Plan p1 = plan_gemm16(rows, n_hid, n_in, true, false, false, 0, wide && x_aligned);
         const Gemm16Plan p2 = plan_gemm16(rows, n_out, n_hid, true, false, false, 0, wide);
-        const Gemm16Plan p3 = plan_gemm16(n_hid, n_out, rows, false, false, true, L.floats_pa, wide);
-        const Gemm16Plan p4 = plan_gemm16(rows, n_hid, n_out, true, true, true, floats_pb, wide);
-        const Gemm16Plan p5 = plan_gemm16(n_in, n_hid, rows, false, false, true, floats_pb, wide_x);
+        const Gemm16Plan p3 = plan_gemm16(n_hid, n_out, rows, false, false, true, L.floats_pa, wide, softmax);
+        const Gemm16Plan p4 = plan_gemm16(rows, n_hid, n_out, true, true, true, floats_pb, wide, softmax);
+        const Gemm16Plan p5 = plan_gemm16(n_in, n_hid, rows, false, false, true, floats_pb, wide && (copy_x || x_aligned));
         Gemm16Args a{};
         MARK(0);
 

@@ -1,4 +1,4 @@
-"""The 256 x 256 tile of the bf16 products (wide16_kernel) where it can go wrong: a partial k step in every product, ragged
+"""The tiles of the bf16 products with steps of 64 k (wide16_kernel) where they can go wrong: a partial k step in every product, ragged
 last tiles, k slices, logits far from zero, labels outside the classes, patterns whose rows are not 16-byte aligned.
 
 Bar: relative L2 1e-2 per tensor, as for every bf16 gradient: H, the output delta and the hidden delta are rounded to bf16
@@ -30,11 +30,14 @@ def _dev(t):
 
 
 @pytest.mark.parametrize("n_in,n_hid,n_out,batch,dense", [
-    (1030, 1100, 1500, 9000, False),    # all five products on the tile; k = 1030, 1100, 1500, 9000: all with a remainder
+    (1030, 1100, 1500, 9000, False),    # all five products on these tiles; k = 1030, 1100, 1500, 9000: all with a remainder
     (1030, 1100, 1500, 4097, True),
     (1088, 1088, 1536, 8192, False),    # no remainder anywhere
     (300, 1300, 2051, 8191, False),     # both backward products of the output layer, remainders 3 and 63
     (400, 480, 3203, 16384, False),     # hidden delta in k slices
+    (400, 480, 3203, 2047, False),      # the 128 x 128 tile for hidden delta and dW2, both in k slices
+    (1024, 520, 1003, 5001, True),      # ... and for hidden and output layer
+    (72, 1000, 40, 6001, True),         # a product shorter than a step
 ])
 def test_gradient(n_in, n_hid, n_out, batch, dense):
     shape = si.MlpShape(n_in, n_hid, n_out, True)
