@@ -329,7 +329,7 @@ constexpr Cfg16Info CFG16_INFO[CFG16_COUNT] = {
     {128, 128, 32, {{8.6, 1.7, 0.0129, 0.0087, 0.91, 1.00, 1.00}, {7.4, 1.2, 0.0183, 0.0098, 0.76, 1.00, 1.22}, {4.9, 0.1, 0.0156, 0.0090, 0.80, 1.00, 1.75}}, "bf16 128x128"},
     {64, 64, 32, {{5.3, 0.5, 0.0057, 0.0036, 0.91, 0.97, 1.00}, {5.1, 0.4, 0.0089, 0.0043, 0.83, 1.00, 1.24}, {4.0, 0.0, 0.0074, 0.0040, 0.89, 1.00, 2.05}}, "bf16 64x64"},
     {256, 256, 64, {{16.0, 14.0, 0.0278, 0.0235, 0.53, 0.47, 1.00}, {9.5, 7.1, 0.0248, 0.0242, 0.72, 0.73, 1.19}, {8.2, 10.0, 0.0240, 0.0228, 0.74, 0.66, 1.45}}, "bf16 256x256"},
-    {128, 128, 64, {{6.4, 2.6, 0.0095, 0.0075, 0.73, 1.00, 1.00}, {5.5, 1.5, 0.0096, 0.0080, 0.75, 0.86, 1.33}, {4.6, 2.4, 0.0104, 0.0079, 0.76, 1.00, 1.47}}, "bf16 128x128k64"},
+    {128, 128, 64, {{6.4, 2.6, 0.0095, 0.0075, 0.73, 1.00, 1.00}, {5.5, 1.5, 0.0096, 0.0080, 0.75, 0.86, 1.33}, {4.6, 2.4, 0.0104, 0.0086, 0.76, 1.00, 1.47}}, "bf16 128x128k64"},
 };
 
 struct Gemm16Plan {
