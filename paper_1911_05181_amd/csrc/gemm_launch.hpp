@@ -1,5 +1,5 @@
 // Launchers of the fp32-operand matrix products.  Each unit's kernels are compiled in a source file of its own
-// (gemm_fp32.hip: the fp32 matrix instruction, gemm_split.hip: three-term bf16 splits), so that they build side by side;
+// (gemm_fp32.hip: the fp32 matrix instruction, gemm_split.hip: three bf16 terms, gemm_half.hip: two f16 terms), so that they build side by side;
 // the planner in ulsnn.hip chooses among the tile shapes numbered here.
 #pragma once
 #include <hip/hip_runtime.h>
