@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libulsnn.so")
 FAST_CALL = os.path.join(HERE, "_fast_call.so")     # argument marshalling of the binding (CPython extension, host only)
-SOURCES = ["ulsnn.hip", "gemm_fp32.hip", "gemm_split.hip", "gemm_half.hip"]
+SOURCES = ["ulsnn.hip", "gemm_fp32.hip", "gemm_split.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -54,8 +54,6 @@ enum Epilogue {
     EPI_MSE_ONLY = 8    // the same sums, C not written
 };
 
-constexpr int GEMM_EXP_UNKNOWN = 1 << 20, GEMM_EXP_UNIT = 15;      // (of elements of at most 1)
-
 struct GemmArgs {
     const float *A, *B;
     float *C;
@@ -68,8 +66,6 @@ struct GemmArgs {
     int kchunk;          // k range handled per blockIdx.y (multiple of BK); >= K when there is no split
     int tiles_m, tiles_n;
     size_t partial_stride;  // EPI_PARTIAL: elements between consecutive partial results
-    // power of two that brings the operand's elements into the range of f16 (gemm_half.hpp), where their bound is known
-    int exp_a = GEMM_EXP_UNKNOWN, exp_b = GEMM_EXP_UNKNOWN;
 };
 
 // WAVES_PER_SIMD_ is the occupancy the register allocation must allow (wavefronts per SIMD).

@@ -1,5 +1,5 @@
 // Launchers of the fp32-operand matrix products.  Each unit's kernels are compiled in a source file of its own
-// (gemm_fp32.hip: the fp32 matrix instruction, gemm_split.hip: three bf16 terms, gemm_half.hip: two f16 terms), so that they build side by side;
+// (gemm_fp32.hip: the fp32 matrix instruction, gemm_split.hip: three-term bf16 splits), so that they build side by side;
 // the planner in ulsnn.hip chooses among the tile shapes numbered here.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -10,8 +10,6 @@ namespace ulsnn {
 
 // Tile shapes of the fp32 instruction (order of ULSNN_TILE_*) and of the split.
 enum CfgId { CFG_256x128 = 0, CFG_128W8, CFG_128, CFG_128x64, CFG_64x128, CFG_64, CFG_64K64, CFG_160x128, CFG_64K32, CFG_COUNT };
-
-enum HalfId { HP_256x256 = 0, HP_256x128, HP_128W8, HP_128, HP_128x64, HP_64x128, HP_64, HP_COUNT };
 
 enum SplitId { SP_256x256 = 0, SP_256x128, SP_128W8, SP_128, SP_128x64, SP_64x128, SP_64, SP_64K64, SP_32K128, SP_COUNT };
 
@@ -25,6 +23,5 @@ constexpr int SPLIT_MAX_LD = (1 << 21) - 64;
 #define ULSNN_HIDDEN __attribute__((visibility("hidden")))
 ULSNN_HIDDEN hipError_t launch_fp32(int cfg, int splits, bool a_kc, bool b_kc, int epi, const GemmArgs &a, hipStream_t s);
 ULSNN_HIDDEN hipError_t launch_split(int cfg, int splits, bool a_kc, bool b_kc, int epi, bool mixed, const GemmArgs &a, hipStream_t s);
-ULSNN_HIDDEN hipError_t launch_half(int cfg, int splits, bool a_kc, bool b_kc, int epi, const GemmArgs &a, hipStream_t s);
 
 }  // namespace ulsnn

@@ -68,11 +68,9 @@ constexpr CfgInfo CFG_INFO[CFG_COUNT] = {
     {64, 64, 32, 512, 4, 0.86, "64x64k32"},
 };
 
-enum class Unit { fp32, split, half };      // gemm.hpp, gemm_split.hpp, gemm_half.hpp
-
 struct GemmPlan {
-    Unit unit;
-    int cfg;         // CfgId, SplitId or HalfId
+    bool split;      // cfg is a SplitId (gemm_split.hpp), else a CfgId (gemm.hpp)
+    int cfg;
     int tiles_m, tiles_n;
     int splits, kchunk;
     double est_us;
@@ -169,32 +167,23 @@ constexpr unsigned ALL_CFGS = (1u << CFG_COUNT) - 1;
 // ---------------------------------------------------------------------------------------------------------
 
 // Run time of a launch that gives every compute unit r workgroups: base + (r - 1) * base_more + chunk * slope(r), with
-// slope(r) = slope_1 (idle + (1 - idle) r) for r <= 1 and slope_r times the rounds beyond, of which the last counts `full` +
-// (1 - full) of its share (microseconds, and microseconds per k).  Fitted, for the bf16 split, to launches with r = 1 .. 5,
-// k = 512 and 2048 in three layouts and, the tiles of 128 rows and more, to 29 products from 2048^3 to 16384 x 16384 x 2048: mostly
-// within 12 % of the measured time where k >= 1000.  For the f16 split to 198 launches with r = 1/4 .. 6, k = 128, 512 and
-// 2048 in three layouts: within 2 to 4 % on average, 14 % at most.  Not modelled: the stores of a large C under a short k (12000 x 5000 x 64 takes
-// 1.5 times what it says, with every tile).
+// slope(r) = slope_1 (idle + (1 - idle) r) for r <= 1 and slope_r times the rounds beyond, the last of which counts 0.6 + 0.4
+// of its share (microseconds, and microseconds per k).  Fitted to launches with r = 1 .. 5, k = 512 and 2048 in three layouts
+// and, the tiles of 128 rows and more, to 29 products from 2048^3 to 16384 x 16384 x 2048: mostly within 12 % of the measured
+// time where k >= 1000, and the tile it chooses within 3 % of the fastest but for two (6 and 7 %).  Not modelled: the stores
+// of a large C under a short k (12000 x 5000 x 64 takes 1.5 times what it says, with every tile).
 struct SplitInfo {
     int bm, bn, bk, threads, occ;
-    double base, base_more, slope_1, slope_r, idle, full;
+    double base, base_more, slope_1, slope_r, idle;
     const char *name;
 };
 constexpr SplitInfo SPLIT_INFO[SP_COUNT] = {
-    {256, 256, 16, 512, 1, 13.5, 8.0, 0.1380, 0.1380, 0.60, 0.60, "256x256"}, {256, 128, 32, 512, 1, 7.5, 5.0, 0.0760, 0.0750, 0.70, 0.60, "256x128"},
-    {128, 128, 32, 512, 1, 5.7, 3.0, 0.0406, 0.0450, 0.75, 0.60, "128x128w8"}, {128, 128, 16, 256, 3, 7.7, 1.0, 0.0445, 0.0405, 0.75, 0.60, "128x128"},
-    {128, 64, 32, 512, 2, 5.9, 0.9, 0.0260, 0.0260, 0.75, 0.60, "128x64"},     {64, 128, 32, 512, 2, 5.9, 0.9, 0.0260, 0.0260, 0.75, 0.60, "64x128"},
-    {64, 64, 32, 256, 3, 4.0, 0.3, 0.0170, 0.0136, 0.75, 0.60, "64x64"},       {64, 64, 64, 512, 1, 4.2, 2.2, 0.0146, 0.0155, 0.75, 0.60, "64x64k64"},
-    {32, 32, 128, 512, 1, 4.2, 3.0, 0.0061, 0.0061, 0.75, 0.60, "32x32k128"},
+    {256, 256, 16, 512, 1, 13.5, 8.0, 0.1380, 0.1380, 0.60, "256x256"}, {256, 128, 32, 512, 1, 7.5, 5.0, 0.0760, 0.0750, 0.70, "256x128"},
+    {128, 128, 32, 512, 1, 5.7, 3.0, 0.0406, 0.0450, 0.75, "128x128w8"}, {128, 128, 16, 256, 3, 7.7, 1.0, 0.0445, 0.0405, 0.75, "128x128"},
+    {128, 64, 32, 512, 2, 5.9, 0.9, 0.0240, 0.0240, 0.75, "128x64"},     {64, 128, 32, 512, 2, 5.9, 0.9, 0.0240, 0.0240, 0.75, "64x128"},
+    {64, 64, 32, 256, 3, 4.0, 0.3, 0.0170, 0.0136, 0.75, "64x64"},       {64, 64, 64, 512, 1, 4.2, 2.2, 0.0146, 0.0155, 0.75, "64x64k64"},
+    {32, 32, 128, 512, 1, 4.2, 3.0, 0.0061, 0.0061, 0.75, "32x32k128"},
 };
-constexpr SplitInfo HALF_INFO[HP_COUNT] = {
-    {256, 256, 32, 512, 1, 16.7, 12.1, 0.0810, 0.0811, 0.75, 0.58, "256x256"}, {256, 128, 32, 1024, 1, 11.5, 7.7, 0.0500, 0.0488, 0.64, 0.59, "256x128"},
-    {128, 128, 32, 512, 2, 7.0, 3.4, 0.0300, 0.0272, 0.83, 0.64, "128x128w8"}, {128, 128, 32, 256, 2, 8.3, 2.6, 0.0345, 0.0270, 0.83, 0.64, "128x128"},
-    {128, 64, 32, 512, 2, 5.5, 2.4, 0.0234, 0.0182, 0.90, 0.72, "128x64"},     {64, 128, 32, 512, 2, 5.5, 2.4, 0.0234, 0.0182, 0.90, 0.72, "64x128"},
-    {64, 64, 32, 256, 4, 5.2, 0.9, 0.0201, 0.0118, 0.89, 1.00, "64x64"},
-};
-// Shortest sum that goes through the f16 split: below it the bf16 split errs less (gemm_half.hpp).
-constexpr int HALF_MIN_K = 128;
 
 double split_model_us(const SplitInfo &c, int m, int n, int k, int splits, int *kchunk_out, int *splits_out)
 {
@@ -206,58 +195,49 @@ double split_model_us(const SplitInfo &c, int m, int n, int k, int splits, int *
     const double r = wgs / num_cu(), whole = std::ceil(r);
     // A round that leaves compute units idle takes less time than a full one: the chip runs at a higher clock (power bounds
     // these kernels), and a shared compute unit takes the next workgroup as soon as one of its own ends.  4608^3 with
-    // 256 x 256 tiles of the bf16 split, 27 % of a second round: 1100 us where two full rounds would take 1300.
-    const double rounds = c.full * whole + (1.0 - c.full) * r;
+    // 256 x 256 tiles, 27 % of a second round: 1100 us where two full rounds would take 1300.
+    const double rounds = 0.6 * whole + 0.4 * r;
     double t = c.base + (whole - 1.0) * c.base_more;
     t += chunk * (r <= 1.0 ? c.slope_1 * (c.idle + (1.0 - c.idle) * r) : c.slope_r * rounds);
     if (sp > 1) t += 3.0 + (double)m * n * (sp + 1.0) * 4.0 / 5.0e6;
     return t;
 }
 
-// `mask`: the tiles of the bf16 split that may be taken.
 GemmPlan plan_split(int m, int n, int k, int split_limit, unsigned mask)
 {
     GemmPlan best{};
     best.est_us = 1e30;
-    const int max_splits = std::max(1, std::min(std::min(64, split_limit), k / 128));
-    auto consider = [&](Unit unit, int cfg, const SplitInfo &c) {
+    best.split = true;
+    for (int ci = 0; ci < SP_COUNT; ++ci) {
+        const SplitInfo &c = SPLIT_INFO[ci];
+        if (!(mask >> ci & 1) || (ci == SP_32K128 && k < c.bk)) continue;   // (a step that would be mostly padding)
+        const int max_splits = std::max(1, std::min(std::min(64, split_limit), k / 128));
         for (int s = 1; s <= max_splits; ++s) {
             int chunk, sp;
             const double us = split_model_us(c, m, n, k, s, &chunk, &sp);
-            if (sp != s || us >= best.est_us || (unit == Unit::half && std::min(chunk, k) < HALF_MIN_K)) continue;
-            best.unit = unit;
-            best.cfg = cfg;
+            if (sp != s || us >= best.est_us) continue;
+            best.cfg = ci;
             best.tiles_m = (m + c.bm - 1) / c.bm;
             best.tiles_n = (n + c.bn - 1) / c.bn;
             best.splits = sp;
             best.kchunk = chunk;
             best.est_us = us;
         }
-    };
-    for (int ci = 0; ci < SP_COUNT; ++ci)      // (32 x 32: not where a step would be mostly padding)
-        if ((mask >> ci & 1) && !(ci == SP_32K128 && k < SPLIT_INFO[ci].bk)) consider(Unit::split, ci, SPLIT_INFO[ci]);
-    for (int ci = 0; ci < HP_COUNT; ++ci) consider(Unit::half, ci, HALF_INFO[ci]);
+    }
     return best;
 }
 
 constexpr unsigned ALL_SPLIT = (1u << SP_COUNT) - 1;
 
-inline const char *plan_name(const GemmPlan &p)
-{
-    return p.unit == Unit::half ? HALF_INFO[p.cfg].name : p.unit == Unit::split ? SPLIT_INFO[p.cfg].name : CFG_INFO[p.cfg].name;
-}
+inline const char *plan_name(const GemmPlan &p) { return p.split ? SPLIT_INFO[p.cfg].name : CFG_INFO[p.cfg].name; }
 
-// Launch a product by its plan (any unit; `mixed`: how the bf16 split takes it).
+// Launch a product by its plan (either unit).
 hipError_t launch_plan(const GemmPlan &p, bool a_kc, bool b_kc, int epi, GemmArgs a, hipStream_t s, bool mixed = false)
 {
     a.tiles_m = p.tiles_m;
     a.tiles_n = p.tiles_n;
     a.kchunk = p.kchunk;
-    switch (p.unit) {
-        case Unit::half: return launch_half(p.cfg, p.splits, a_kc, b_kc, epi, a, s);
-        case Unit::split: return launch_split(p.cfg, p.splits, a_kc, b_kc, epi, mixed, a, s);
-        default: return launch_fp32(p.cfg, p.splits, a_kc, b_kc, epi, a, s);
-    }
+    return p.split ? launch_split(p.cfg, p.splits, a_kc, b_kc, epi, mixed, a, s) : launch_fp32(p.cfg, p.splits, a_kc, b_kc, epi, a, s);
 }
 
 // Longest k that one workgroup sums through the split.  Its downward rounding grows with k (1.1e-11 k of the result) where
@@ -465,7 +445,7 @@ GemmPlan plan_sgemm_ws(int m, int n, int k, bool a_kc, bool b_kc, int lda, int l
     const GemmPlan one = plan_sgemm(m, n, k, a_kc, b_kc, lda, ldb);
     if (slices < 2) return one;
     const int limit = (int)std::min<size_t>(64, slices);
-    if (one.unit == Unit::fp32) {
+    if (!one.split) {
         const GemmPlan cut = plan_product(m, n, k, a_kc, b_kc, lda, ldb, limit);
         return (cut.splits > 1 && cut.est_us < 0.8 * one.est_us) ? cut : one;
     }
@@ -722,7 +702,7 @@ int mlp_grad_impl(const ulsnn_mlp_desc *d, const void *W1v, const void *W2v, con
         // Z = H W2 + b2   (softmax form)   or   Y = tanh(H W2 + b2)   (the paper's form)
         a = GemmArgs{};
         a.A = H; a.lda = L.ldh; a.B = W2; a.ldb = n_out; a.C = Z; a.ldc = L.ldz;
-        a.M = rows; a.N = n_out; a.K = n_hid; a.alpha = 1.f; a.beta = 0.f; a.bias = d->b2; a.exp_a = GEMM_EXP_UNIT;
+        a.M = rows; a.N = n_out; a.K = n_hid; a.alpha = 1.f; a.beta = 0.f; a.bias = d->b2;
         HIP_TRY(launch_plan(P.g2, true, false, ts ? EPI_BIAS_TANH : EPI_BIAS, a, s));
         MARK(2);
 
@@ -781,8 +761,6 @@ int mlp_grad_impl(const ulsnn_mlp_desc *d, const void *W1v, const void *W2v, con
         a3.M = n_hid; a3.N = n_out; a3.K = rows; a3.alpha = 1.f; a3.beta = beta;
         a4.A = Z; a4.lda = L.ldz; a4.B = W2; a4.ldb = n_out; a4.C = dA1; a4.ldc = L.ldh;
         a4.M = rows; a4.N = n_hid; a4.K = n_out; a4.alpha = 1.f; a4.beta = 0.f; a4.aux = H; a4.ldaux = L.ldh;
-        a3.exp_a = GEMM_EXP_UNIT;
-        if (!ts) a3.exp_b = a4.exp_a = GEMM_EXP_UNIT;      // a probability, less one at the label
         {
             GemmArgs p3 = a3, p4 = a4;
             if (P.g4.splits > 1) { p4.C = part_b; p4.partial_stride = (size_t)a4.M * a4.N; }
