@@ -286,8 +286,13 @@ using T16_64 = Tile16<64, 64, 2, 2, 8>;      // 256 threads, 8 workgroups / CU
 using T16_256x256 = Wide16<256, 256, 4, 2, 2>;
 using T16_256x256t = Wide16<256, 256, 2, 4, 2>;
 using T16_128k64 = Wide16<128, 128, 4, 2, 4>;
+// For patterns whose rows are not 16-byte aligned and find no room for an aligned copy: such a product fetches element by element
+// and is bound by that, so the tile that fetches least per product wins.  dW1 against the best of 128 x 128 and 64 x 64: 785 x 256
+// over 65536 patterns 243 us (396), 2049 x 1024 over 20000 488 (789), 4001 x 1000 over 9000 396 (693); hidden layer 65536 x 256 x 785
+// 177 (246), 30000 x 500 x 3001 665 (910).
+using T16_256x256u = Tile16<256, 256, 4, 2, 2>;
 
-enum Cfg16Id { CFG16_128 = 0, CFG16_64, CFG16_256x256, CFG16_128K64, CFG16_COUNT };
+enum Cfg16Id { CFG16_128 = 0, CFG16_64, CFG16_256x256, CFG16_128K64, CFG16_256x256U, CFG16_COUNT };
 
 // One launch on an otherwise idle chip, in microseconds, by the layout of its operands (0 a k-contiguous A and an m-contiguous B,
 // 1 both k-contiguous, 2 both m-contiguous): `base`, `more` per further round of workgroups, and per k of the longest slice
@@ -300,16 +305,22 @@ enum Cfg16Id { CFG16_128 = 0, CFG16_64, CFG16_256x256, CFG16_128K64, CFG16_COUNT
 struct Tile16Cost {
     double base, more, slope_1, slope_r, idle, full, delta;
 };
+// `loose`: the same where the rows of A are not 16-byte aligned (a k-contiguous A, and an m-contiguous one): each element is a load of
+// its own, five to ten times the cost per k.  Fitted to 1800 launches of 74 products (49 to 4001 inputs, 700 to 65536 patterns); the
+// choice takes 0.6 and 1.6 percent longer than the best measured, the costs of aligned rows 5 and 41.
 struct Cfg16Info {
     int bm, bn, bk;
-    Tile16Cost cost[3];
+    Tile16Cost cost[3], loose[2];      // (a slope of zero: not offered)
     const char *name;
 };
 constexpr Cfg16Info CFG16_INFO[CFG16_COUNT] = {
-    {128, 128, 32, {{8.6, 1.7, 0.0129, 0.0087, 0.91, 1.00, 1.00}, {7.4, 1.2, 0.0183, 0.0098, 0.76, 1.00, 1.22}, {4.9, 0.1, 0.0156, 0.0090, 0.80, 1.00, 1.75}}, "bf16 128x128"},
-    {64, 64, 32, {{5.3, 0.5, 0.0057, 0.0036, 0.91, 0.97, 1.00}, {5.1, 0.4, 0.0089, 0.0043, 0.83, 1.00, 1.24}, {4.0, 0.0, 0.0074, 0.0040, 0.89, 1.00, 2.05}}, "bf16 64x64"},
-    {256, 256, 64, {{16.0, 14.0, 0.0278, 0.0235, 0.53, 0.47, 1.00}, {9.5, 7.1, 0.0248, 0.0242, 0.72, 0.73, 1.19}, {8.2, 10.0, 0.0240, 0.0228, 0.74, 0.66, 1.45}}, "bf16 256x256"},
-    {128, 128, 64, {{6.4, 2.6, 0.0095, 0.0075, 0.73, 1.00, 1.00}, {5.5, 1.5, 0.0096, 0.0080, 0.75, 0.86, 1.33}, {4.6, 2.4, 0.0104, 0.0086, 0.76, 1.00, 1.47}}, "bf16 128x128k64"},
+    {128, 128, 32, {{8.6, 1.7, 0.0129, 0.0087, 0.91, 1.00, 1.00}, {7.4, 1.2, 0.0183, 0.0098, 0.76, 1.00, 1.22}, {4.9, 0.1, 0.0156, 0.0090, 0.80, 1.00, 1.75}},
+     {{2.9, 0.0, 0.1633, 0.0984, 0.64, 1.00, 1.00}, {3.1, 0.0, 0.1104, 0.0628, 0.76, 1.00, 1.00}}, "bf16 128x128"},
+    {64, 64, 32, {{5.3, 0.5, 0.0057, 0.0036, 0.91, 0.97, 1.00}, {5.1, 0.4, 0.0089, 0.0043, 0.83, 1.00, 1.24}, {4.0, 0.0, 0.0074, 0.0040, 0.89, 1.00, 2.05}},
+     {{2.0, 0.0, 0.0656, 0.0392, 0.86, 1.00, 1.00}, {5.7, 0.0, 0.0454, 0.0301, 0.84, 1.00, 1.00}}, "bf16 64x64"},
+    {256, 256, 64, {{16.0, 14.0, 0.0278, 0.0235, 0.53, 0.47, 1.00}, {9.5, 7.1, 0.0248, 0.0242, 0.72, 0.73, 1.19}, {8.2, 10.0, 0.0240, 0.0228, 0.74, 0.66, 1.45}}, {}, "bf16 256x256"},
+    {128, 128, 64, {{6.4, 2.6, 0.0095, 0.0075, 0.73, 1.00, 1.00}, {5.5, 1.5, 0.0096, 0.0080, 0.75, 0.86, 1.33}, {4.6, 2.4, 0.0104, 0.0086, 0.76, 1.00, 1.47}}, {}, "bf16 128x128k64"},
+    {256, 256, 32, {}, {{2.0, 0.0, 0.2185, 0.2176, 0.84, 1.00, 1.00}, {2.0, 0.0, 0.1582, 0.1571, 0.95, 0.90, 1.00}}, "bf16 256x256u"},
 };
 
 struct Gemm16Plan {
@@ -319,10 +330,12 @@ struct Gemm16Plan {
     double est_us;
 };
 
-// `wide`: the operands suit wide16_kernel, which loads whole vectors with 32-bit offsets within a panel of 256 rows: 16-byte
-// aligned rows shorter than WIDE16_MAX_LD.  `delta`: the product forms the output delta while loading.
+// `rows`: ROWS16_WIDE where the operands suit wide16_kernel, which loads whole vectors with 32-bit offsets within a panel of 256
+// rows: 16-byte aligned rows shorter than WIDE16_MAX_LD.  ROWS16_LOOSE where those of A are not aligned (never with both operands
+// k-contiguous).  `delta`: the product forms the output delta while loading.
 constexpr int WIDE16_MAX_LD = 1 << 22;
-Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_split, size_t max_partial_floats, bool wide, bool delta = false)
+enum Rows16 { ROWS16_WIDE, ROWS16_ALIGNED, ROWS16_LOOSE };
+Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_split, size_t max_partial_floats, Rows16 rows, bool delta = false)
 {
     Gemm16Plan best{};
     best.est_us = 1e30;
@@ -330,8 +343,9 @@ Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_spl
     if ((size_t)m * n > 0) max_splits = (int)std::min<size_t>(max_splits, std::max<size_t>(1, max_partial_floats / ((size_t)m * n)));
     for (int ci = 0; ci < CFG16_COUNT; ++ci) {
         const Cfg16Info &c = CFG16_INFO[ci];
-        if (c.bk == 64 && !wide) continue;
-        const Tile16Cost &t = c.cost[a_kc && b_kc ? 1 : a_kc ? 0 : 2];
+        if (c.bk == 64 && rows != ROWS16_WIDE) continue;
+        const Tile16Cost &t = rows == ROWS16_LOOSE ? c.loose[a_kc ? 0 : 1] : c.cost[a_kc && b_kc ? 1 : a_kc ? 0 : 2];
+        if (t.slope_1 == 0.0) continue;
         const int tiles_m = (m + c.bm - 1) / c.bm, tiles_n = (n + c.bn - 1) / c.bn;
         for (int s = 1; s <= max_splits; ++s) {
             const int chunk = (int)round_up((size_t)(std::max(k, 1) + s - 1) / s, c.bk);
@@ -394,39 +408,41 @@ hipError_t launch_gemm16(const Gemm16Plan &p, bool a_kc, bool b_kc, int epi, Gem
     auto go = [&](auto cfg) -> hipError_t {
         using Cfg = decltype(cfg);
         if (epi == EPI_BIAS_TANH && a_kc && !b_kc) return launch16_one<Cfg, true, false, EPI_BIAS_TANH>(a, p.splits, s);
-        if (epi == EPI_BIAS && a_kc && !b_kc) return launch16_one<Cfg, true, false, EPI_BIAS>(a, p.splits, s);
-        if ((epi == EPI_BIAS_STATS || epi == EPI_STATS_ONLY) && a_kc && !b_kc) {
-            // one statistics group per wavefront column; the logits' rows must be 16-byte aligned
-            if (a.stat_groups != (a.N + Cfg::WTN - 1) / Cfg::WTN || a.stat_stride < (size_t)a.M || !a.stats || !a.label_logit || !a.labels ||
-                (epi == EPI_BIAS_STATS && !a.c_vec))
+        if (epi == EPI_PARTIAL && !a_kc && !b_kc && !a.row_lse) return launch16_one<Cfg, false, false, EPI_PARTIAL>(a, p.splits, s);
+        if (epi == EPI_AXPBY && !a_kc && !b_kc && !a.row_lse) return launch16_one<Cfg, false, false, EPI_AXPBY>(a, p.splits, s);
+        if constexpr (!std::is_same_v<Cfg, T16_256x256u>) {
+            if (epi == EPI_BIAS && a_kc && !b_kc) return launch16_one<Cfg, true, false, EPI_BIAS>(a, p.splits, s);
+            if ((epi == EPI_BIAS_STATS || epi == EPI_STATS_ONLY) && a_kc && !b_kc) {
+                // one statistics group per wavefront column; the logits' rows must be 16-byte aligned
+                if (a.stat_groups != (a.N + Cfg::WTN - 1) / Cfg::WTN || a.stat_stride < (size_t)a.M || !a.stats || !a.label_logit || !a.labels ||
+                    (epi == EPI_BIAS_STATS && !a.c_vec))
+                    return hipErrorInvalidValue;
+                return epi == EPI_BIAS_STATS ? launch16_one<Cfg, true, false, EPI_BIAS_STATS>(a, p.splits, s)
+                                             : launch16_one<Cfg, true, false, EPI_STATS_ONLY>(a, p.splits, s);
+            }
+            if ((epi == EPI_TANH_MSE || epi == EPI_MSE_ONLY) && a_kc && !b_kc) {
+                if (a.stat_groups != (a.N + Cfg::WTN - 1) / Cfg::WTN || a.stat_stride < (size_t)a.M || !a.stats || !a.targets || a.ldt < a.N ||
+                    (epi == EPI_TANH_MSE && !a.c_vec))
+                    return hipErrorInvalidValue;
+                return epi == EPI_TANH_MSE ? launch16_one<Cfg, true, false, EPI_TANH_MSE>(a, p.splits, s)
+                                           : launch16_one<Cfg, true, false, EPI_MSE_ONLY>(a, p.splits, s);
+            }
+            if (a.row_lse) {   // a product that forms the output delta from the logits while loading them
+                if (!a.aligned || !a.labels) return hipErrorInvalidValue;
+                if (a_kc && b_kc && epi == EPI_TANHGRAD) return launch16_one<Cfg, true, true, EPI_TANHGRAD, 1>(a, p.splits, s);
+                if (a_kc && b_kc && epi == EPI_PARTIAL) return launch16_one<Cfg, true, true, EPI_PARTIAL, 1>(a, p.splits, s);
+                if (!a_kc && !b_kc && epi == EPI_PARTIAL) return launch16_one<Cfg, false, false, EPI_PARTIAL, 2>(a, p.splits, s);
+                if (!a_kc && !b_kc && epi == EPI_AXPBY) return launch16_one<Cfg, false, false, EPI_AXPBY, 2>(a, p.splits, s);
                 return hipErrorInvalidValue;
-            return epi == EPI_BIAS_STATS ? launch16_one<Cfg, true, false, EPI_BIAS_STATS>(a, p.splits, s)
-                                         : launch16_one<Cfg, true, false, EPI_STATS_ONLY>(a, p.splits, s);
+            }
+            if (epi == EPI_TANHGRAD && a_kc && b_kc) return launch16_one<Cfg, true, true, EPI_TANHGRAD>(a, p.splits, s);
+            if (epi == EPI_PARTIAL && a_kc && b_kc) return launch16_one<Cfg, true, true, EPI_PARTIAL>(a, p.splits, s);
         }
-        if ((epi == EPI_TANH_MSE || epi == EPI_MSE_ONLY) && a_kc && !b_kc) {
-            if (a.stat_groups != (a.N + Cfg::WTN - 1) / Cfg::WTN || a.stat_stride < (size_t)a.M || !a.stats || !a.targets || a.ldt < a.N ||
-                (epi == EPI_TANH_MSE && !a.c_vec))
-                return hipErrorInvalidValue;
-            return epi == EPI_TANH_MSE ? launch16_one<Cfg, true, false, EPI_TANH_MSE>(a, p.splits, s)
-                                       : launch16_one<Cfg, true, false, EPI_MSE_ONLY>(a, p.splits, s);
-        }
-        if (a.row_lse) {   // a product that forms the output delta from the logits while loading them
-            if (!a.aligned || !a.labels) return hipErrorInvalidValue;
-            if (a_kc && b_kc && epi == EPI_TANHGRAD) return launch16_one<Cfg, true, true, EPI_TANHGRAD, 1>(a, p.splits, s);
-            if (a_kc && b_kc && epi == EPI_PARTIAL) return launch16_one<Cfg, true, true, EPI_PARTIAL, 1>(a, p.splits, s);
-            if (!a_kc && !b_kc && epi == EPI_PARTIAL) return launch16_one<Cfg, false, false, EPI_PARTIAL, 2>(a, p.splits, s);
-            if (!a_kc && !b_kc && epi == EPI_AXPBY) return launch16_one<Cfg, false, false, EPI_AXPBY, 2>(a, p.splits, s);
-            return hipErrorInvalidValue;
-        }
-        if (epi == EPI_TANHGRAD && a_kc && b_kc) return launch16_one<Cfg, true, true, EPI_TANHGRAD>(a, p.splits, s);
-        if (epi == EPI_PARTIAL && a_kc && b_kc) return launch16_one<Cfg, true, true, EPI_PARTIAL>(a, p.splits, s);
-        if (epi == EPI_PARTIAL && !a_kc && !b_kc) return launch16_one<Cfg, false, false, EPI_PARTIAL>(a, p.splits, s);
-        if (epi == EPI_AXPBY && !a_kc && !b_kc) return launch16_one<Cfg, false, false, EPI_AXPBY>(a, p.splits, s);
         return hipErrorInvalidValue;
     };
-    if (CFG16_INFO[p.cfg].bk == 64 && (!a.aligned || (c_bf16 && !a.c_vec))) return hipErrorInvalidValue;   // (plan_gemm16's `wide`)
+    if (CFG16_INFO[p.cfg].bk == 64 && (!a.aligned || (c_bf16 && !a.c_vec))) return hipErrorInvalidValue;   // (plan_gemm16's ROWS16_WIDE)
     return p.cfg == CFG16_128 ? go(T16_128{}) : p.cfg == CFG16_256x256 ? go(T16_256x256{})
-         : p.cfg == CFG16_128K64 ? go(T16_128k64{}) : go(T16_64{});
+         : p.cfg == CFG16_128K64 ? go(T16_128k64{}) : p.cfg == CFG16_256x256U ? go(T16_256x256u{}) : go(T16_64{});
 }
 
 // Plan of an unsplit ulsnn_sgemm.
@@ -867,14 +883,16 @@ int mlp_grad_impl16(const ulsnn_mlp_desc *d, const u16 *W1, const u16 *W2, const
         const bool copy_x = !rows_16b_aligned(Xs, n_in) && (task.backward ? rows >= 128 : n_in > 64) &&
                             (size_t)rows * ldx_copy * sizeof(u16) <= half_pb * sizeof(float);
         const size_t floats_pb = copy_x ? half_pb : L.floats_pb;
-        // (The copies of the weights and everything in the workspace are aligned.  The hidden layer goes by the patterns as they
-        // came, so that an error with and without gradient has the same sums whether or not they are copied.)
-        const bool wide = std::max(std::max(n_in, n_hid), n_out) <= WIDE16_MAX_LD - 32, x_aligned = rows_16b_aligned(Xs, n_in), softmax = !ts;
-        const Gemm16Plan p1 = plan_gemm16(rows, n_hid, n_in, true, false, false, 0, wide && x_aligned);
+        // (The copies of the weights and everything in the workspace are aligned.  The hidden layer of patterns that did not come
+        // aligned stays on the steps of 32 k, whose sums do not depend on the tile, so that an error with and without gradient has
+        // the same whether or not they are copied.)
+        const bool x_aligned = rows_16b_aligned(Xs, n_in), softmax = !ts;
+        const Rows16 wide = std::max(std::max(n_in, n_hid), n_out) <= WIDE16_MAX_LD - 32 ? ROWS16_WIDE : ROWS16_ALIGNED;
+        const Gemm16Plan p1 = plan_gemm16(rows, n_hid, n_in, true, false, false, 0, x_aligned ? wide : copy_x ? ROWS16_ALIGNED : ROWS16_LOOSE);
         const Gemm16Plan p2 = plan_gemm16(rows, n_out, n_hid, true, false, false, 0, wide);
         const Gemm16Plan p3 = plan_gemm16(n_hid, n_out, rows, false, false, true, L.floats_pa, wide, softmax);
         const Gemm16Plan p4 = plan_gemm16(rows, n_hid, n_out, true, true, true, floats_pb, wide, softmax);
-        const Gemm16Plan p5 = plan_gemm16(n_in, n_hid, rows, false, false, true, floats_pb, wide && (copy_x || x_aligned));
+        const Gemm16Plan p5 = plan_gemm16(n_in, n_hid, rows, false, false, true, floats_pb, copy_x || x_aligned ? wide : ROWS16_LOOSE);
         Gemm16Args a{};
         MARK(0);
 

@@ -1,5 +1,6 @@
 """The tiles of the bf16 products with steps of 64 k (wide16_kernel) where they can go wrong: a partial k step in every product, ragged
-last tiles, k slices, logits far from zero, labels outside the classes, patterns whose rows are not 16-byte aligned.
+last tiles, k slices, logits far from zero, labels outside the classes, patterns whose rows are not 16-byte aligned; and the 256 x 256
+tile with steps of 32 k, for such patterns where no copy of them fits into the workspace.
 
 Bar: relative L2 1e-2 per tensor, as for every bf16 gradient: H, the output delta and the hidden delta are rounded to bf16
 (2^-9 relative each, so about 3.4e-3 where the three do not average out); three of 3203 classes lost would be 3e-2.
@@ -76,3 +77,31 @@ def test_far_logits_and_a_partial_step():
     torch.cuda.synchronize()
     assert not res.dW1.any() and not res.db1.any()
     assert _rel(res.dW2, ref.dW2) <= TOL and _rel(res.db2, ref.db2) <= TOL
+
+
+@pytest.mark.parametrize("n_in,n_hid,n_out,batch", [
+    (785, 251, 10, 45001),      # hidden layer and dW1, the latter in k slices; 785 = 3 * 256 + 17, 45001 = 32 * 1406 + 9
+    (6001, 1500, 10, 5700),     # dW1 in one slice
+    (785, 251, 40, 70001),      # two passes over the patterns: the second adds to the first's dW1
+])
+def test_unaligned_patterns_that_are_not_copied(n_in, n_hid, n_out, batch):
+    """Rows of an odd number of bf16 elements, too many for an aligned copy (it would have to fit into half of the slices' region
+    of the workspace, 64 MB here)."""
+    assert min(batch, 65536) * (n_in + 7) * 2 > 64 << 20
+    g = torch.Generator(device=DEV).manual_seed(3)
+    W1 = (torch.randn(n_in, n_hid, generator=g, device=DEV) / n_in ** 0.5).bfloat16()
+    W2 = (torch.randn(n_hid, n_out, generator=g, device=DEV) / n_hid ** 0.5).bfloat16()
+    X = torch.randn(batch, n_in, generator=g, device=DEV).bfloat16()
+    y = torch.randint(0, n_out, (batch,), generator=g, device=DEV, dtype=torch.int32)
+    res, again = ulsnn.mlp_grad(W1, W2, X, y), ulsnn.mlp_grad(W1, W2, X, y)
+    H = torch.tanh(X.double() @ W1.double())
+    L = torch.log_softmax(H @ W2.double(), 1)
+    D = L.exp()
+    D[torch.arange(batch, device=DEV), y.long()] -= 1
+    dA = (D @ W2.double().t().contiguous()) * (1 - H * H)
+    for got, want in ((res.dW1, X.double().t().contiguous() @ dA), (res.dW2, H.t().contiguous() @ D)):
+        assert (got.double() - want).norm() <= TOL * want.norm()
+    loss = -L[torch.arange(batch, device=DEV), y.long()].sum()
+    assert abs(res.loss.double() - loss) <= TOL * loss
+    assert torch.equal(ulsnn.mlp_loss(W1, W2, X, y), res.loss)
+    assert torch.equal(res.dW1, again.dW1) and torch.equal(res.dW2, again.dW2)
