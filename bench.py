@@ -12,8 +12,8 @@ reported as "settle_steps"): for its first ~40 ms under load a fresh process run
 square sizes of the second workload (reported under "sgemm").
 
 "roofline" describes the dominant stage of the step: the matrix products that take the most time, timed live with
-HIP events recorded on the launch stream (ulsnn_mlp_grad_timed).  An fp32 product runs as three f16 matrix products on
-a two-term split of its operands, so its bound is a third of the dense f16 matrix peak: 838.9 TFLOP/s at the nominal
+HIP events recorded on the launch stream (ulsnn_mlp_grad_timed).  An fp32 product runs as six bf16 matrix products on
+a three-term split of its operands, so its bound is a sixth of the dense bf16 matrix peak: 419.4 TFLOP/s at the nominal
 2.4 GHz and, as "frac_at_measured_clock", the same flop per clock and compute unit at the shader clock a probe
 wavefront measured while the step was running ("device").  The "frac_of_fp32_mfma_peak" fields compare with the rate of
 the fp32 matrix instructions (157.3 TFLOP/s nominal), which the split may exceed.
@@ -35,7 +35,7 @@ if ROOT not in sys.path:
 
 PEAK_FP32_MFMA_TFLOPS = 157.3      # 256 CUs x 256 flop/clk/CU x 2.4 GHz
 FLOP_PER_CLK_PER_CU = 256          # fp32 matrix instructions
-SPLIT_FLOP_PER_CLK_PER_CU = 4096 / 3                # fp32 products as three f16 matrix products
+SPLIT_FLOP_PER_CLK_PER_CU = 4096 / 6                # fp32 products as six bf16 matrix products
 PEAK_SPLIT_TFLOPS = 256 * SPLIT_FLOP_PER_CLK_PER_CU * 2.4e9 / 1e12
 # HBM bytes per launch of each stage's kernels (calibrated rocprofv3 counters) are read from this summary at run time:
 # its lines "bench_traffic: stage=<name> bytes_per_launch=<n>".
@@ -430,7 +430,7 @@ def main():
     dom = max(stage_flops, key=lambda k: acc[k])
     achieved = stage_flops[dom] / (acc[dom] * 1e-3) / 1e12
     split_at_clock = peak_at_clock * SPLIT_FLOP_PER_CLK_PER_CU / FLOP_PER_CLK_PER_CU if peak_at_clock else None
-    roofline = {"bound": "mfma", "kernel": f"fp32 products (three f16 matrix products each) of stage '{dom}'",
+    roofline = {"bound": "mfma", "kernel": f"fp32 products (six bf16 matrix products each) of stage '{dom}'",
                 "achieved": round(achieved, 2),
                 "peak": round(PEAK_SPLIT_TFLOPS, 1), "unit": "TFLOP/s", "frac": round(achieved / PEAK_SPLIT_TFLOPS, 4),
                 "frac_at_measured_clock": round(achieved / split_at_clock, 4) if split_at_clock else None,
