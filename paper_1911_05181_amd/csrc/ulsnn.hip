@@ -337,6 +337,10 @@ struct Gemm16Plan {
 // rows: 16-byte aligned rows shorter than WIDE16_MAX_LD.  ROWS16_LOOSE where those of A are not aligned (never with both operands
 // k-contiguous).  `delta`: the product forms the output delta while loading.
 constexpr int WIDE16_MAX_LD = 1 << 22;
+// Hidden and output layers of up to three steps of 64 k: the loop has too few to hide its loads, and the tile's epilogue is the longer
+// (output layer 4096 x 1000 x 64: 10.3 us, 64 x 64 7.5; hidden layer 4096 x 700 x 48: 7.9 and 6.7).  Over 260 such calls of k = 32 to 160
+// (1024 to 65536 patterns, 64 to 3200 columns) the best tile with steps of 32 k is 0.06 us behind the best of all.
+constexpr int WIDE16_FORWARD_MIN_K = 161;
 enum Rows16 { ROWS16_WIDE, ROWS16_ALIGNED, ROWS16_LOOSE };
 Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_split, size_t max_partial_floats, Rows16 rows, bool delta = false)
 {
@@ -346,7 +350,7 @@ Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_spl
     if ((size_t)m * n > 0) max_splits = (int)std::min<size_t>(max_splits, std::max<size_t>(1, max_partial_floats / ((size_t)m * n)));
     for (int ci = 0; ci < CFG16_COUNT; ++ci) {
         const Cfg16Info &c = CFG16_INFO[ci];
-        if (c.bk == 64 && rows != ROWS16_WIDE) continue;
+        if (c.bk == 64 && (rows != ROWS16_WIDE || (!b_kc && a_kc && k < WIDE16_FORWARD_MIN_K))) continue;
         const Tile16Cost &t = rows == ROWS16_LOOSE ? c.loose[a_kc ? 0 : 1] : c.cost[a_kc && b_kc ? 1 : a_kc ? 0 : 2];
         if (t.slope_1 == 0.0) continue;
         const int tiles_m = (m + c.bm - 1) / c.bm, tiles_n = (n + c.bn - 1) / c.bn;
