@@ -304,13 +304,17 @@ enum Cfg16Id { CFG16_128 = 0, CFG16_64, CFG16_256x256, CFG16_128K64, CFG16_256x2
 // delta), 2.3 (dW2) and 1.2 (dW1); one matrix rate for all layouts, which stood here, by 2, 15, 11 and 5.
 // `delta_base`: what forming the delta adds to `base`: over 180 dW2 products of 32 to 800 hidden units, 64 to 3203 classes and 256 to
 // 8192 patterns, the 128 x 128 tile with steps of 64 k was taken 29 times where 64 x 64 is 0.7 to 3.5 us faster, now 5 times.
+// `waits`: a latency of so many rounds that every `held` rounds, which a compute unit works on together, have once.
 struct Tile16Cost {
     double base, more, slope_1, slope_r, idle, full, delta;
-    double delta_base = 0.0;
+    double delta_base = 0.0, waits = 0.0, held = 1.0;
 };
 // `loose`: the same where the rows of A are not 16-byte aligned (a k-contiguous A, and an m-contiguous one): each element is a load of
 // its own, five to ten times the cost per k.  Fitted to 1800 launches of 74 products (49 to 4001 inputs, 700 to 65536 patterns); the
-// choice takes 0.6 and 1.6 percent longer than the best measured, the costs of aligned rows 5 and 41.
+// choice takes 0.6 and 1.6 percent longer than the best measured, the costs of aligned rows 5 and 41.  The round costs of 64 x 64 (eight
+// workgroups a compute unit) and of dW1 on 128 x 128 (four) are fitted apart, to 120 products of 20 to 300 hidden units: without `waits`
+// several rounds at once seemed to gain nothing, so dW1 of 2049 x 100 over 65536 patterns was cut into 30 slices (383 us, 59 take 320), of
+// 1017 x 34 into 32 (64 take 20 us less), and the hidden layer 45001 x 72 x 1017 went to 128 x 128 (204 us, 64 x 64 170).
 struct Cfg16Info {
     int bm, bn, bk;
     Tile16Cost cost[3], loose[2];      // (a slope of zero: not offered)
@@ -318,9 +322,9 @@ struct Cfg16Info {
 };
 constexpr Cfg16Info CFG16_INFO[CFG16_COUNT] = {
     {128, 128, 32, {{8.6, 1.7, 0.0129, 0.0087, 0.91, 1.00, 1.00}, {7.4, 1.2, 0.0183, 0.0098, 0.76, 1.00, 1.22}, {4.9, 0.1, 0.0156, 0.0090, 0.80, 1.00, 1.75}},
-     {{2.9, 0.0, 0.1633, 0.0984, 0.64, 1.00, 1.00}, {3.1, 0.0, 0.1104, 0.0628, 0.76, 1.00, 1.00}}, "bf16 128x128"},
+     {{2.9, 0.0, 0.1633, 0.0984, 0.64, 1.00, 1.00}, {3.1, 0.0, 0.1104, 0.0500, 0.76, 0.50, 1.00, 0.0, 0.90, 4.0}}, "bf16 128x128"},
     {64, 64, 32, {{5.3, 0.5, 0.0057, 0.0036, 0.91, 0.97, 1.00}, {5.1, 0.4, 0.0089, 0.0043, 0.83, 1.00, 1.24}, {4.0, 0.0, 0.0074, 0.0040, 0.89, 1.00, 2.05}},
-     {{2.0, 0.0, 0.0656, 0.0392, 0.86, 1.00, 1.00}, {5.7, 0.0, 0.0454, 0.0301, 0.84, 1.00, 1.00}}, "bf16 64x64"},
+     {{2.0, 0.0, 0.0656, 0.0235, 0.86, 0.50, 1.00, 0.0, 2.60, 8.0}, {5.7, 0.0, 0.0454, 0.0227, 0.84, 0.50, 1.00, 0.0, 0.86, 8.0}}, "bf16 64x64"},
     {256, 256, 64, {{16.0, 14.0, 0.0278, 0.0235, 0.53, 0.47, 1.00}, {9.5, 7.1, 0.0248, 0.0242, 0.72, 0.73, 1.19}, {8.2, 10.0, 0.0240, 0.0228, 0.74, 0.66, 1.45}}, {}, "bf16 256x256"},
     {128, 128, 64, {{6.4, 2.6, 0.0095, 0.0075, 0.73, 1.00, 1.00}, {5.5, 1.5, 0.0096, 0.0080, 0.75, 0.86, 1.33}, {4.6, 2.4, 0.0104, 0.0086, 0.76, 1.00, 1.47, 0.8}}, {}, "bf16 128x128k64"},
     {256, 256, 32, {}, {{2.0, 0.0, 0.2185, 0.2176, 0.84, 1.00, 1.00}, {2.0, 0.0, 0.1582, 0.1571, 0.95, 0.90, 1.00}}, "bf16 256x256u"},
@@ -359,7 +363,7 @@ Gemm16Plan plan_gemm16(int m, int n, int k, bool a_kc, bool b_kc, bool allow_spl
             if ((std::max(k, 1) + chunk - 1) / chunk != s) continue;      // (fewer slices, seen already)
             const double r = (double)tiles_m * tiles_n * s / num_cu(), whole = std::ceil(r), slope = delta ? t.delta : 1.0;
             double us = t.base + (delta ? t.delta_base : 0.0) + (whole - 1.0) * t.more;
-            us += chunk * slope * (r <= 1.0 ? t.slope_1 * (t.idle + (1.0 - t.idle) * r) : t.slope_r * (t.full * whole + (1.0 - t.full) * r));
+            us += chunk * slope * (r <= 1.0 ? t.slope_1 * (t.idle + (1.0 - t.idle) * r) : t.slope_r * (t.waits * std::ceil(r / t.held) + t.full * whole + (1.0 - t.full) * r));
             us += (double)m * n * s * (s > 1 || !a_kc ? 4.0 : 2.0) / 8.0e6;      // its stores, beyond what `base` has
             if (s > 1) us += 3.0 + (double)m * n * (s + 1.0) * 4.0 / 5.0e6;       // the reduction
             if (us < best.est_us) {

@@ -83,6 +83,8 @@ def test_far_logits_and_a_partial_step():
     (785, 251, 10, 45001),      # hidden layer and dW1, the latter in k slices; 785 = 3 * 256 + 17, 45001 = 32 * 1406 + 9
     (6001, 1500, 10, 5700),     # dW1 in one slice
     (785, 251, 40, 70001),      # two passes over the patterns: the second adds to the first's dW1
+    (1017, 72, 10, 45001),      # a narrow hidden layer: 64 x 64 tiles of it, 128 x 128 of dW1
+    (1017, 34, 31, 68383),      # 64 x 64 tiles of both, dW1 in 64 slices; the second pass is copied
 ])
 def test_unaligned_patterns_that_are_not_copied(n_in, n_hid, n_out, batch):
     """Rows of an odd number of bf16 elements, too many for an aligned copy (it would have to fit into half of the slices' region
