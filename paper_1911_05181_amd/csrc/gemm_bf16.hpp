@@ -98,8 +98,8 @@ struct Tile16 {
 // alignment of every read
 template <bool KC, int R>
 struct Panel16 {
-    // KC: rows of 32 + 8 elements.  MC: k rows 8 banks (32 B) apart modulo the 32 banks, so the four k rows a
-    // 16-lane group of the transpose read touches cover all banks once (R + 8 gave 2-way conflicts).
+    // KC: rows of 32 + 8 elements.  MC: k rows 32 B apart modulo the banks (R + 8, 16 B apart, is slower).  Conflicts remain: 0.75 to 1.0
+    // cycles per cycle of LDS work in the counters of both layouts' kernels; layouts without any gain nothing (LDS is not the bound).
     static constexpr int LD = KC ? (32 + 8) : (R + 16);
     static constexpr int SIZE = KC ? R * LD : 32 * LD;
 };
